@@ -8,12 +8,12 @@
 // gather[r] / kdiv of the unpermuted input: then the permutation is folded
 // into the operand loads and x_perm is never written.
 //
-// bf16, many rows per expert (MFMA-bound): 8 waves (2 per SIMD) on a 256-row
-// tile, v_mfma_f32_32x32x16_bf16 with fp32 accumulation, operands staged
-// through two LDS stages.  Loads use buffer resources whose range ends where
-// the valid rows / K end, so ragged tiles read zeros without branches.  The
-// MFMA computes D = W_tile * A_tile^T: each lane holds 4 consecutive output
-// columns of one row.  The expert and row range of a workgroup come from the
+// bf16, many rows per expert: 8 waves (2 per SIMD) on a 256-row tile,
+// v_mfma_f32_16x16x32_bf16 with fp32 accumulation, operands staged through two
+// LDS stages.  Loads use buffer resources whose range ends where the valid
+// rows / K end, so ragged tiles read zeros without branches.  The MFMA computes
+// D = W_tile * A_tile^T: each lane holds 4 consecutive output columns of one
+// row.  The expert and row range of a workgroup come from the
 // device-side offsets (one wave prefix sum over per-expert tile counts), so no
 // host sync is needed.
 //
@@ -23,27 +23,27 @@
 
 #include "lds_dma.hpp"
 
-// LDS-DMA large-M kernel: (BM, BN, WM, WN, BK, LDS stages, waves that issue
-// the DMA (0 = all), M-tile group of the tile order, persistent)
+// LDS-DMA large-M kernel: (BM, BN, WM, WN, LDS stages, M-tile group of the tile
+// order, persistent)
 #ifndef FOE_DMA_GU
-#define FOE_DMA_GU 256, 128, 2, 4, 64, 2, 4, 4, 1
+#define FOE_DMA_GU 256, 128, 2, 4, 2, 4, 1
 #endif
 #ifndef FOE_DMA_DN
-#define FOE_DMA_DN 256, 256, 2, 4, 64, 2, 4, 4, 1
+#define FOE_DMA_DN 256, 256, 2, 4, 2, 4, 1
 #endif
 // plain grouped GEMM over a few wide segments (the q/k/v projection of the
 // attention groups): as the down projection, tiles walked XCD by XCD
 #ifndef FOE_DMA_SEG
-#define FOE_DMA_SEG 256, 256, 2, 4, 64, 2, 4, 4, 2
+#define FOE_DMA_SEG 256, 256, 2, 4, 2, 4, 2
 #endif
 // plain GEMM with the residual epilogue (few M rows: 128 x 256 tiles, or
 // 128 x 128 when the larger tiles would leave compute units idle); one tile
 // per CU walks all of K, so a third LDS stage keeps more loads in flight
 #ifndef FOE_DMA_RES
-#define FOE_DMA_RES 128, 256, 2, 4, 64, 3, 3, 4, 1
+#define FOE_DMA_RES 128, 256, 2, 4, 3, 4, 1
 #endif
 #ifndef FOE_DMA_RES_SMALL
-#define FOE_DMA_RES_SMALL 128, 128, 2, 4, 64, 3, 4, 4, 1
+#define FOE_DMA_RES_SMALL 128, 128, 2, 4, 3, 4, 1
 #endif
 // few rows per expert (decode): LDS-staged weight stream with NS stages, K
 // walk rotated per workgroup, and (block decode form) pair lists built in the
@@ -264,53 +264,60 @@ __device__ __forceinline__ int src_row(const int32_t* __restrict__ gather, int k
 // explicit vmcnt waits (the compiler does not see them; the kernel issues no
 // other global loads inside the main loop and uses M0 nowhere else).
 //
-// LDS layout of a tile: rows of BK bf16 (no padding), the 16-byte chunk c of
-// row r stored in slot c ^ swz(r).  A fragment read (32 rows, one chunk) then
-// touches every bank group once per 16 lanes.  Since a DMA instruction
-// writes 1 KiB contiguously, the swizzle is applied on the load side: the
-// lane that lands in slot s of row r fetches chunk s ^ swz(r).
+// LDS layout of a tile: rows of 64 bf16 (no padding), the 16-byte chunk c of
+// row r stored in slot c ^ swz_tile(r).  A fragment read takes one chunk of 16
+// rows, two rows to a 256-byte bank line, so the eight rows of each half need
+// eight different slots.  Since a DMA instruction writes 1 KiB contiguously,
+// the swizzle is applied on the load side: the lane that lands in slot s of
+// row r fetches chunk s ^ swz_tile(r).
+__device__ __forceinline__ int swz_tile(int r) { return (r >> 1) & 7; }
 
-template <int BM, int BN, int WM, int WN, bool GATEUP, int BK, int NST, int PW>
+template <int BM, int BN, int WM, int WN, bool GATEUP, int NST>
 struct DmaCfg {
+  static constexpr int BK = 64;            // K columns per stage: whole 128-byte lines
   static constexpr int NW = WM * WN, NTHR = NW * kWave;
-  static constexpr int NP = PW > 0 ? PW : NW;  // waves that issue the DMA
   static constexpr int WTM = BM / WM, WTN = BN / WN;
-  static constexpr int SM = WTM / 32, SN = WTN / 32;
+  static constexpr int SM = WTM / 16, SN = WTN / 16;  // 16-row / 16-column sub-tiles
   static constexpr int NB = GATEUP ? 2 : 1;
+  static constexpr int NJ = NB * SN;       // weight fragments of a k32 step
+  static constexpr int SH = SM / 2;        // A fragments of a row half
   static constexpr int RB = BK * 2;        // bytes per tile row
   static constexpr int CPR = BK / 8;       // 16-byte chunks per row
   static constexpr int RPI = 1024 / RB;    // rows per DMA instruction
   static constexpr int A_INS = BM / RPI, B_INS = BN / RPI;  // DMA instructions per tile
-  static constexpr int NLD = (A_INS + NB * B_INS) / NP;      // per issuing wave
-  // the swizzle of a row depends on row & 15, so on instruction ii through
-  // ii & (NVAR - 1)
-  static constexpr int NVAR = RPI >= 16 ? 1 : 16 / RPI;
+  // DMA instructions per wave and stage: weights, and each row half of A
+  static constexpr int WPW = NB * B_INS / NW, AH = A_INS / 2 / NW;
+  static constexpr int NLD = WPW + 2 * AH;
   static constexpr int A_BYTES = BM * RB, B_BYTES = BN * RB;
   static constexpr int STAGE = A_BYTES + NB * B_BYTES;
-  static constexpr int KS = BK / 16;       // k16 steps per stage
-  static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be a multiple of 32");
-  static_assert(BM % RPI == 0 && BN % RPI == 0 && (A_INS + NB * B_INS) % NP == 0 && NP <= NW,
-                "even DMA split");
-  // with several issuing waves, the instructions of one wave stay inside one
-  // tile and start at a multiple of NVAR (a single issuing wave maps every
-  // instruction to its tile at compile time)
-  static_assert(NP == 1 || (A_INS % NLD == 0 && B_INS % NLD == 0 && NLD % NVAR == 0),
-                "one tile per issuing wave");
-  static_assert(KS % 2 == 0, "fragment slots alternate within a stage");
-  static_assert(NST >= 2 && NLD * (NST - 2) <= 63, "vmcnt range");
+  static_assert(WTM % 32 == 0 && WTN % 16 == 0, "wave tile");
+  static_assert(NB * B_INS % NW == 0 && A_INS % (2 * NW) == 0, "even DMA split");
+  static_assert(B_INS % WPW == 0 && (WTM / 16) % AH == 0,
+                "a wave's instructions stay inside one weight slice and one run of A rows");
+  static_assert(NST >= 2 && NLD * NST <= 63, "vmcnt range");
   static_assert(NST * STAGE <= 160 * 1024, "LDS capacity");
 };
 
-// Stage kt (K columns kt*BK ..) lives in LDS buffer kt % NST.  Iteration kt:
-//   issue the DMA of stage kt+NST-1 into the buffer freed by stage kt-1;
-//   k16 steps 0..KS-2 of stage kt (fragment reads one step ahead);
-//   wait for stage kt+1 and meet the other waves;
-//   read the first fragments of stage kt+1; k16 step KS-1 of stage kt.
-// Only the first PW waves (one per SIMD when PW = 4) issue DMA instructions.
-// The address unit of a CU takes a stage's instructions at a fixed rate, and
-// a wave whose instruction finds its queue full stops issuing; when every
-// wave loads, both waves of a SIMD stall together and its MFMA pipe idles.
-// With producer waves, the other wave of each SIMD keeps issuing MFMAs.
+// acc += w x^T on v_mfma_f32_16x16x32_bf16, the accumulator fixed in AGPRs.
+// (Through the builtin the register allocator gives each result other
+// registers than its addend and spills around 60 of them inside the K loop.)
+// The compiler does not see an MFMA here: acc_fence() separates the
+// accumulators' first write and last read from the MFMAs by more wait states
+// than the instruction needs; inside the loop an accumulator returns after at
+// least three other MFMAs.
+__device__ __forceinline__ void mma16(f32x4& acc, bf16x8 w, bf16x8 x) {
+  asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
+}
+template <int N>
+__device__ __forceinline__ void acc_fence(f32x4* a) {
+  static_assert(N % 8 == 0, "eight accumulators per statement");
+#pragma unroll
+  for (int i = 0; i < N; i += 8)
+    asm volatile("s_nop 15\n\ts_nop 15"
+                 : "+a"(a[i]), "+a"(a[i + 1]), "+a"(a[i + 2]), "+a"(a[i + 3]), "+a"(a[i + 4]),
+                   "+a"(a[i + 5]), "+a"(a[i + 6]), "+a"(a[i + 7]));
+}
+
 // Residual epilogue of the plain (non gate/up) form: the output becomes
 // scale * (acc + x), x an fp32 matrix of the output's shape.
 struct GemmResid {
@@ -347,14 +354,48 @@ struct GemmArgs {
 // carry that cache policy (kScDevice: written through past the XCD's L2, so
 // that other XCDs can read the tile once the stores have completed).  The
 // two-slice form (GemmArgs::halves) always stores as usual, staged through LDS.
-template <int BM, int BN, int WM, int WN, bool GATEUP, int BK, int NST, int PW, bool RESID,
-          int OUT_CPOL>
-__device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs& g, const int e,
-                                          const int row0, const int row_end, const int ntile,
+//
+// Stage kt (64 K columns) lives in LDS buffer kt % NST.  What bounds the loop
+// is the delivery of the operands: a 256 x 256 tile needs 64 KiB per stage,
+// which takes longer to arrive than the stage's MFMAs take, so the loads must
+// be in flight well over one iteration ahead.  With two stage buffers that
+// needs each part of a buffer to be free as early as possible.  An iteration
+// therefore runs in four quarters, each wave's rows taken as two halves:
+//   Q1  A half 0, k 0-31    reads: A half 0 k 32-63, weights k 32-63
+//       barrier: A half 1 has landed; nobody reads A half 0 and the weights
+//       of this stage any more
+//   Q2  A half 0, k 32-63   reads: A half 1 k 0-31
+//   Q3  A half 1, k 0-31    reads: A half 1 k 32-63
+//       (Q2, Q3 issue the weights and A half 0 of stage kt+NST)
+//       barrier: weights and A half 0 of stage kt+1 have landed; nobody reads
+//       A half 1 of this stage any more
+//   Q4  A half 1, k 32-63   reads: next stage's A half 0 and weights, k 0-31
+//       (issues A half 1 of stage kt+NST)
+// so every load has between NST-1 and NST-0.5 iterations to arrive (whole
+// stages in two buffers left it half to three quarters of one), the waits are
+// counted (vmcnt) and never drain the queue, and each row's 64 columns are one
+// whole 128-byte line.  Fused expert FFN, against the loop with whole stages
+// (us): 2110 -> 1950 at 65536 rows x 32 experts, d 4096, F 1536 (1.17 -> 1.27
+// PFLOP/s); 775 -> 735 at 65536 rows x 64 experts, d 2048, F 1024; 207 -> 198
+// at 16384 skewed rows x 16 experts.  Without the vmcnt waits (timing only) it
+// is no faster; with the loads alone it takes 1490, with the MFMAs and
+// fragment reads alone 1630: what is left is the two sharing the clock that
+// the power limit allows (1.85 GHz) and the tiles' beginnings and ends.
+// 16x16x32 MFMAs: a register-only loop reaches 2.04 PFLOP/s with them and 1.86
+// with 32x32x16 ones.
+template <int BM, int BN, int WM, int WN, bool GATEUP, int NST, bool RESID, int OUT_CPOL>
+__device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs& g, const int e_,
+                                          const int row0_, const int row_end_, const int ntile_,
                                           int32_t* signal = nullptr) {
   static_assert(!(RESID && GATEUP), "residual epilogue on the plain form only");
-  using C = DmaCfg<BM, BN, WM, WN, GATEUP, BK, NST, PW>;
-  constexpr int NLD = C::NLD;
+  using C = DmaCfg<BM, BN, WM, WN, GATEUP, NST>;
+  constexpr int BK = C::BK, WPW = C::WPW, AH = C::AH, NLD = C::NLD;
+  // the tile is the same for the whole workgroup: its coordinates (read from
+  // LDS) and what follows from them stay in scalar registers
+  const int e = __builtin_amdgcn_readfirstlane(e_);
+  const int row0 = __builtin_amdgcn_readfirstlane(row0_);
+  const int row_end = __builtin_amdgcn_readfirstlane(row_end_);
+  const int ntile = __builtin_amdgcn_readfirstlane(ntile_);
   const bf16* __restrict__ A = g.A;
   const int32_t* __restrict__ gather = g.gather;
   const int kdiv = g.kdiv, a_rows = g.a_rows, N = g.N, K = g.K;
@@ -363,437 +404,390 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs& g
   bf16* __restrict__ out = g.out;
   const GemmResid& res = g.res;
 
-  const int tid = threadIdx.x;
-  const int lane = lane_id();
-  const int wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  {
-    const int n0 = ntile * BN;
+  // opaque: what follows from the lane is formed anew for every tile instead
+  // of being kept (spilled) across the persistent loop
+  const int tid = opaque_int((int)threadIdx.x);
+  const int lane = tid & (kWave - 1);
+  const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave_u / WN, wn = wave_u % WN;
+  const int n0 = ntile * BN;
 
-    const int n_valid = min(BN, N - n0);
-    // operand ranges: A rows (a per-tile range, or the whole source when
-    // gathering), then one weight slice per matrix
-    const bf16* t_base[1 + C::NB];
-    uint32_t t_bytes[1 + C::NB];
-    t_base[0] = gather == nullptr ? A + (size_t)row0 * K : A;
-    t_bytes[0] = gather == nullptr ? (uint32_t)min(BM, row_end - row0) * K * 2u
-                                   : (uint32_t)a_rows * K * 2u;
-    t_base[1] = B0 + ((size_t)e * N + n0) * K;
-    t_bytes[1] = (uint32_t)n_valid * K * 2u;
-    if constexpr (GATEUP) {
-      t_base[2] = B1 + ((size_t)e * N + n0) * K;
-      t_bytes[2] = t_bytes[1];
-      if (g.halves) {
-        // the two slices of a 2*BN-column tile of B0 (a slice past N is empty)
-        const int h0 = ntile * 2 * BN, h1 = min(h0 + BN, N);
-        t_base[1] = B0 + ((size_t)e * N + h0) * K;
-        t_bytes[1] = (uint32_t)max(min(BN, N - h0), 0) * K * 2u;
-        t_base[2] = B0 + ((size_t)e * N + h1) * K;
-        t_bytes[2] = (uint32_t)max(min(BN, N - h1), 0) * K * 2u;
-      }
-    }
-
-    // DMA instruction gq of a stage covers RPI rows (1 KiB) of the A tile
-    // (gq < A_INS) or of a weight tile.  Lane l lands in row rl = l/CPR, slot
-    // l%CPR of the instruction's rows and so fetches chunk (l%CPR) ^ swz(row);
-    // the swizzle depends on the instruction only through its variant
-    // ii & (NVAR-1), so each lane keeps NVAR chunk choices.  Gathered A rows
-    // keep one source offset per A instruction.
-    const int rl = lane / C::CPR, cl = lane % C::CPR;
-    int chunk[C::NVAR];
-    uint32_t lane_off[C::NVAR];
+  // This wave's DMA: instructions wave*WPW .. of the weight slices and
+  // wave*AH .. of each row half of A.  An instruction covers RPI rows (1 KiB);
+  // lane l lands in row l / CPR, slot l % CPR and fetches chunk
+  // (l % CPR) ^ swz_tile(row).
+  const int rl = lane / C::CPR, cl = lane % C::CPR;
+  auto kcol = [&](int ii) { return (cl ^ swz_tile(ii * C::RPI + rl)) * 8; };
+  // weights: slice ws, its instruction wi0; a slice past N is empty
+  const int wp = wave_u * WPW, ws = wp / C::B_INS, wi0 = wp % C::B_INS;
+  int wrow0 = n0;  // first row of the slice
+  const bf16* wmat = B0;
+  if constexpr (GATEUP) {
+    if (g.halves) wrow0 = ntile * 2 * BN + ws * BN;
+    else if (ws == 1) wmat = B1;
+  }
+  wrow0 = min(wrow0, N);
+  const uint64_t w_base = (uint64_t)(uintptr_t)(wmat + ((size_t)e * N + wrow0) * K);
+  const uint32_t w_bytes = (uint32_t)min(BN, N - wrow0) * K * 2u;
+  // A: the tile's rows, or the whole source when gathering
+  const uint64_t a_base =
+      (uint64_t)(uintptr_t)(gather == nullptr ? A + (size_t)row0 * K : A);
+  const uint32_t a_bytes = gather == nullptr ? (uint32_t)min(BM, row_end - row0) * K * 2u
+                                             : (uint32_t)a_rows * K * 2u;
+  // instruction q of row half h: rows of one 16-row run after another of the
+  // wave rows' halves
+  auto a_ins = [&](int h, int q) {
+    const int t = wave_u * AH + q;
+    constexpr int RUN = C::WTM / 16;  // instructions of half a wave tile's rows
+    return (t / RUN) * 2 * RUN + h * RUN + t % RUN;
+  };
+  uint32_t off_w[WPW], off_a[2][AH];
 #pragma unroll
-    for (int v = 0; v < C::NVAR; ++v) {
-      chunk[v] = cl ^ swz<C::CPR>(v * C::RPI + rl);
-      lane_off[v] = ((uint32_t)rl * K + chunk[v] * 8) * 2u;
-    }
-    constexpr int NV = C::NVAR;
-    const uint32_t row_step = (uint32_t)C::RPI * K * 2u;  // bytes between instructions
-    auto a_src = [&](int ii) {  // gathered source offset of A instruction ii
-      const int r = ii * C::RPI + rl;
-      const int s = (row0 + r < row_end) ? src_row(gather, kdiv, row0 + r, a_rows) : -1;
-      return s < 0 ? kOob : ((uint32_t)s * K + chunk[ii & (NV - 1)] * 8) * 2u;
-    };
-    const uint32_t smem_base = lds_addr(smem);
-
-    // Several issuing waves: wave p loads instructions p*NLD .. p*NLD+NLD-1,
-    // all inside tile tw starting at its instruction ii0.
-    // Share p goes to wave (p + 4) mod NP.  With eight issuing waves, waves
-    // 0..3 (the older wave of each SIMD) take the weight shares and waves
-    // 4..7 the A rows (measured 1% faster at the prefill load than the other
-    // way round, the same elsewhere; results identical).  With four issuing
-    // waves this is the identity; with three (the residual GEMM) each share
-    // moves to the next wave.
-#ifndef FOE_DMA_ROT
-#define FOE_DMA_ROT 4
-#endif
-    const int p = C::NP > 1 ? (min(wave_u, C::NP - 1) + FOE_DMA_ROT) % C::NP : 0;
-    const int tw = p * NLD < C::A_INS ? 0 : 1 + (p * NLD - C::A_INS) / C::B_INS;
-    const int ii0 = tw == 0 ? p * NLD : (p * NLD - C::A_INS) % C::B_INS;
-    const __amdgpu_buffer_rsrc_t rsrc_w =
-        make_rsrc_u(tw == 0 ? t_base[0] : (tw == 1 ? t_base[1] : t_base[C::NB]),
-                    tw == 0 ? t_bytes[0] : (tw == 1 ? t_bytes[1] : t_bytes[C::NB]));
-    const uint32_t lds_w = (tw == 0 ? 0 : C::A_BYTES + (tw - 1) * C::B_BYTES) + ii0 * 1024;
-    const bool gather_a = tw == 0 && gather != nullptr;
-    // source byte offset of this lane's chunk in instruction q (K slab 0)
-    uint32_t off_q[C::NP > 1 ? NLD : 1];
-    if constexpr (C::NP > 1) {
+  for (int q = 0; q < WPW; ++q)
+    off_w[q] = ((uint32_t)((wi0 + q) * C::RPI + rl) * K + kcol(wi0 + q)) * 2u;
 #pragma unroll
-      for (int q = 0; q < NLD; ++q)
-        off_q[q] = gather_a ? a_src(ii0 + q)
-                            : (uint32_t)(ii0 + q) * row_step + lane_off[q & (NV - 1)];
-    }
-    // A single issuing wave: instruction q is fixed at compile time.
-    __amdgpu_buffer_rsrc_t rsrc_t[1 + C::NB];
-    uint32_t a_off[C::NP == 1 ? C::A_INS : 1];
-    if constexpr (C::NP == 1) {
+  for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int t = 0; t <= C::NB; ++t) rsrc_t[t] = make_rsrc_u(t_base[t], t_bytes[t]);
-#pragma unroll
-      for (int ii = 0; ii < C::A_INS; ++ii)
-        a_off[ii] = gather != nullptr ? a_src(ii) : (uint32_t)ii * row_step + lane_off[ii & (NV - 1)];
-    }
-
-    // DMA instruction q (of this issuing wave) of stage kt into LDS buffer
-    // buf; stages past K read zeros
-    const uint32_t lds_base = smem_base + lds_w;
-    auto issue_one = [&](int kt, int buf, int q) {
-      const int k0 = kt * BK;
-      if constexpr (C::NP == 1) {
-        const int tb = q < C::A_INS ? 0 : 1 + (q - C::A_INS) / C::B_INS;
-        const int ii = q < C::A_INS ? q : (q - C::A_INS) % C::B_INS;
-        const uint32_t off =
-            tb == 0 ? a_off[ii] : (uint32_t)ii * row_step + lane_off[ii & (NV - 1)];
-        const bool ok = k0 + chunk[ii & (NV - 1)] * 8 < K && off != kOob;
-        dma16(rsrc_t[tb], ok ? off + (uint32_t)k0 * 2u : kOob, smem_base,
-              buf * C::STAGE + (tb == 0 ? 0 : C::A_BYTES + (tb - 1) * C::B_BYTES) + ii * 1024);
+    for (int q = 0; q < AH; ++q) {
+      const int ii = a_ins(h, q), r = ii * C::RPI + rl;
+      if (gather == nullptr) {
+        off_a[h][q] = ((uint32_t)r * K + kcol(ii)) * 2u;
       } else {
-        const bool ok = k0 + chunk[q & (NV - 1)] * 8 < K && off_q[q] != kOob;
-        dma16(rsrc_w, ok ? off_q[q] + (uint32_t)k0 * 2u : kOob, lds_base,
-              buf * C::STAGE + q * 1024);
+        const int s = (row0 + r < row_end) ? src_row(gather, kdiv, row0 + r, a_rows) : -1;
+        off_a[h][q] = s < 0 ? kOob : ((uint32_t)s * K + kcol(ii)) * 2u;
       }
-    };
+    }
+  const uint32_t smem_base = lds_addr(smem);
+  const uint32_t lds_w = smem_base + C::A_BYTES + ws * C::B_BYTES + wi0 * 1024;
+  const uint32_t lds_a[2] = {smem_base + a_ins(0, 0) * 1024, smem_base + a_ins(1, 0) * 1024};
 
-    f32x16 acc[C::NB][C::SM][C::SN];
+  // The resource of a stage starts at its first K column (scalar arithmetic),
+  // so the per-lane offsets stay fixed; its range shrinks with it and is empty
+  // past K.  In a stage that K ends inside, the lanes past K (and in every
+  // later stage all lanes) read zeros: their offsets are spoilt once.
+  // (signed, below 2^31: the range stays in scalar instructions.  A vector
+  // instruction that wrote it would need wait states before the loads, which
+  // the compiler cannot see)
+  auto stage_rsrc = [&](uint64_t base, uint32_t bytes, int kt) {
+    const int k2 = kt * BK * 2;
+    return make_rsrc_u(reinterpret_cast<const void*>((uintptr_t)(base + (uint32_t)k2)),
+                       (uint32_t)max((int)bytes - k2, 0));
+  };
+  auto tail_w = [&](int kt) {
+    if ((kt + 1) * BK > K) {
 #pragma unroll
-    for (int b = 0; b < C::NB; ++b)
+      for (int q = 0; q < WPW; ++q)
+        if (kt * BK + kcol(wi0 + q) >= K) off_w[q] = kOob;
+    }
+  };
+  auto tail_a = [&](int h, int kt) {
+    if ((kt + 1) * BK > K) {
 #pragma unroll
-      for (int i = 0; i < C::SM; ++i)
-#pragma unroll
-        for (int j = 0; j < C::SN; ++j)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) acc[b][i][j][v] = 0.f;
+      for (int q = 0; q < AH; ++q)
+        if (kt * BK + kcol(a_ins(h, q)) >= K) off_a[h][q] = kOob;
+    }
+  };
+  auto issue_w = [&](const __amdgpu_buffer_rsrc_t& r, int buf, int q) {
+    dma16(r, off_w[q], lds_w, buf * C::STAGE + q * 1024);
+  };
+  auto issue_a = [&](const __amdgpu_buffer_rsrc_t& r, int buf, int h, int q) {
+    dma16(r, off_a[h][q], lds_a[h], buf * C::STAGE + q * 1024);
+  };
 
-    // fragment rows are congruent to lane%32 modulo 32, so one swizzle per lane
-    const int lrow = lane & 31;
-    const int sw = swz<C::CPR>(lrow) ^ (lane >> 5);
-    int xo[C::KS];
+  constexpr int SM = C::SM, SN = C::SN, NJ = C::NJ, SH = C::SH;
+  f32x4 acc[C::NB][SM][SN];
 #pragma unroll
-    for (int ks = 0; ks < C::KS; ++ks) xo[ks] = ((2 * ks) ^ sw) * 16;
-    const int a_row = (wm * C::WTM + lrow) * C::RB;
-    const int b_row = C::A_BYTES + (wn * C::WTN + lrow) * C::RB;
-    bf16x8 xa[2][C::SM];
-    bf16x8 wf[2][C::NB][C::SN];
-    auto fload = [&](int buf, int ks, int slot) {
-      const unsigned char* sa = smem + buf * C::STAGE;
+  for (int b = 0; b < C::NB; ++b)
 #pragma unroll
-      for (int i = 0; i < C::SM; ++i)
-        xa[slot][i] = *reinterpret_cast<const bf16x8*>(sa + a_row + xo[ks] + i * 32 * C::RB);
+    for (int i = 0; i < SM; ++i)
 #pragma unroll
-      for (int b = 0; b < C::NB; ++b)
-#pragma unroll
-        for (int j = 0; j < C::SN; ++j)
-          wf[slot][b][j] = *reinterpret_cast<const bf16x8*>(sa + b_row + xo[ks] + b * C::B_BYTES +
-                                                            j * 32 * C::RB);
-    };
-    constexpr int NM = C::NB * C::SM * C::SN;  // MFMAs per k16 step
-    constexpr int NR = C::SM + C::NB * C::SN;  // fragment reads per k16 step
-    constexpr int NT = NM > NR ? NM : NR;  // slots of a k16 step
-    // Valid 32-row sub-tiles of this wave's WTM rows: a partly filled tile
-    // (an expert's last rows) skips the MFMAs and A fragment reads of the
-    // sub-tiles past row_end (a variant of the loop; full tiles run without
-    // the checks).
-    const int smv = min(max((row_end - row0 - wm * C::WTM + 31) / 32, 0), C::SM);
-    const bool partial_tile = __builtin_amdgcn_readfirstlane(row_end - row0) < BM;
-    // One k16 step in a fixed order: (in an issuing wave) the DMA
-    // instructions [q0, q1) of stage dkt (buffer dbuf) spread evenly over the
-    // MFMAs, each ahead of its MFMA so that it does not queue behind it for the
-    // SIMD's matrix pipe (measured 1-2% faster than after it), then MFMA t of
-    // fragment slot `slot`, then fragment read t of (rbuf, rks) into the other
-    // slot (rks >= 0).  mode: bit 0 issuing wave, bit 1 partly filled tile.
-    auto kstep = [&](auto mode, int slot, int rbuf, int rks, int dkt, int dbuf, int q0,
-                     int q1) {
-      constexpr bool producer = decltype(mode)::value & 1, part = decltype(mode)::value & 2;
-      const unsigned char* sa = smem + rbuf * C::STAGE;
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        if constexpr (producer) {
-#pragma unroll
-          for (int q = q0; q < q1; ++q)
-            if ((q - q0) * NT / (q1 - q0) == t) issue_one(dkt, dbuf, q);
-        }
-        if (t < NM) {
-          const int b = t / (C::SN * C::SM), j = (t / C::SM) % C::SN, i = t % C::SM;
-          if (!part || i < smv)
-            acc[b][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[slot][b][j], xa[slot][i],
-                                                                   acc[b][i][j], 0, 0, 0);
-        }
-        if (rks >= 0 && t < NR) {
-          if (t < C::SM) {
-            if (!part || t < smv)
-              xa[slot ^ 1][t] =
-                  *reinterpret_cast<const bf16x8*>(sa + a_row + xo[rks] + t * 32 * C::RB);
-          } else {
-            const int u = t - C::SM, ub = u / C::SN, uj = u % C::SN;
-            wf[slot ^ 1][ub][uj] = *reinterpret_cast<const bf16x8*>(
-                sa + b_row + xo[rks] + ub * C::B_BYTES + uj * 32 * C::RB);
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
+      for (int j = 0; j < SN; ++j) acc[b][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // K steps rounded up to a multiple of NST: steps past K read zeros.
-    // The DMA of stage kt+NST-1 is spread over the k16 steps of iteration kt:
-    // with more than two stages it may use every step.  With two stages it
-    // must be complete at this iteration's barrier, and (EARLY) its first QE
-    // instructions already go out in the last k16 step of iteration kt-1:
-    // that step follows the barrier after which no wave reads the buffer of
-    // stage kt-1 any more, so the loads of a stage start one k16 step sooner
-    // and have about half as long again to arrive (the stage waits at the
-    // barrier were most of what separated the loop from the MFMA rate).
-    // DS = steps carrying the rest, Q(s) = first instruction of step s,
-    // BEFORE = instructions issued before the barrier.
-    const int nk = ((K + BK - 1) / BK + NST - 1) / NST * NST;
-    constexpr int KS = C::KS;
-    constexpr bool EARLY = NST == 2 && KS >= 3;
-#ifndef FOE_DMA_EARLY_Q  // eighths of a stage's instructions issued early
-#define FOE_DMA_EARLY_Q 4
-#endif
-    constexpr int QE = EARLY ? NLD * FOE_DMA_EARLY_Q / 8 : 0;
-    constexpr int DS = EARLY ? 1 : (NST == 2 ? (KS - 2 > 1 ? KS - 2 : 1) : KS);
-    constexpr int BEFORE = NST == 2 ? NLD : (KS - 1) * NLD / KS;
-    // loads allowed in flight at the barrier of iteration kt (stage kt+1
-    // complete): the later stages' DMAs issued so far
-    constexpr int VM_AT_BARRIER = NST == 2 ? 0 : (NST - 3) * NLD + BEFORE;
-    static_assert(VM_AT_BARRIER <= 63, "vmcnt range");
-    auto qof = [&](int st) { return st >= DS ? NLD : QE + st * (NLD - QE) / DS; };
-    auto iteration = [&](auto mode, int kt, int b) {
-      const int dkt = kt + NST - 1, dbuf = (b + NST - 1) % NST;
+  // LDS offsets of fragment 0 in every buffer and k32 step (fragment rows are
+  // congruent to lane % 16 modulo 16, so one swizzle per lane); opaque, so
+  // that the fragments are reached by the instructions' offset fields (seen
+  // through, each fragment past 64 KiB got an address register of its own)
+  const int lrow = lane & 15;
+  int oa[NST][2], ob[NST][2];
 #pragma unroll
-      for (int st = 0; st + 1 < KS; ++st)
-        kstep(mode, st & 1, b, st + 1, dkt, dbuf, qof(st), qof(st + 1));
-      vm_barrier<VM_AT_BARRIER>();
-      if constexpr (EARLY)  // stage kt+2 into the buffer of stage kt
-        kstep(mode, (KS - 1) & 1, (b + 1) % NST, 0, kt + 2, b, 0, QE);
-      else
-        kstep(mode, (KS - 1) & 1, (b + 1) % NST, 0, dkt, dbuf, qof(KS - 1), qof(KS));
-    };
-    // the K loop, specialised for issuing and non-issuing waves (both meet
-    // the same barriers)
-    auto k_loop = [&](auto mode) {
-      if constexpr (decltype(mode)::value & 1) {
+  for (int b = 0; b < NST; ++b)
 #pragma unroll
-        for (int st = 0; st < NST - 1; ++st)
+    for (int ks = 0; ks < 2; ++ks) {
+      const int x = ((4 * ks + (lane >> 4)) ^ swz_tile(lrow)) * 16 + b * C::STAGE;
+      oa[b][ks] = opaque_int((wm * C::WTM + lrow) * C::RB + x);
+      ob[b][ks] = opaque_int(C::A_BYTES + (wn * C::WTN + lrow) * C::RB + x);
+    }
+  bf16x8 xa[2][SH];  // A fragments of this and of the next quarter
+  bf16x8 wf[2][NJ];  // weight fragments of k32 step 0 and 1
+  auto read_a = [&](int buf, int ks, int h, int i) {
+    xa[ks][i] = *reinterpret_cast<const bf16x8*>(smem + oa[buf][ks] + (h * SH + i) * 16 * C::RB);
+  };
+  auto read_w = [&](int buf, int ks, int u) {
+    wf[ks][u] = *reinterpret_cast<const bf16x8*>(smem + ob[buf][ks] + (u / SN) * C::B_BYTES +
+                                                 (u % SN) * 16 * C::RB);
+  };
+  // Rows of this wave's tile that exist: with at most half of them the wave
+  // leaves out its second half's MFMAs and fragment reads (a variant of the
+  // loop; it meets the same barriers).
+  const bool half_only = row_end - row0 - wm * C::WTM <= C::WTM / 2;
+
+  // K steps rounded up to a multiple of NST: steps past K read zeros.
+  const int nk = ((K + BK - 1) / BK + NST - 1) / NST * NST;
+  constexpr int QM = SH * NJ;       // MFMAs per quarter
+  constexpr int NWA = WPW + AH;     // DMA instructions of Q2 and Q3
+  constexpr int VM = (NST - 1) * NLD;  // loads in flight behind the awaited ones
+  auto iteration = [&](auto hv, int kt, int b) {
+    constexpr bool half = decltype(hv)::value;
+    const int bn = (b + 1) % NST;  // buffer of the next stage
+    const int dkt = kt + NST;      // the stage loaded into this buffer
+    // quarter q: MFMAs of A half q/2, k32 step q%2, each followed by up to one
+    // fragment read (nr of them: rd(n)) and, ahead of it so that it does not
+    // queue behind the MFMA, up to one DMA instruction (dma(slot))
+    auto quarter = [&](auto qv, auto&& dma, int nr, auto&& rd) {
+      constexpr int q = decltype(qv)::value, h = q / 2, ks = q % 2;
+      if constexpr (half && h == 1) {
 #pragma unroll
-          for (int q = 0; q < NLD; ++q) issue_one(st, st, q);
-        if constexpr (EARLY) {  // the early part of stage 1
+        for (int n = 0; n < QM; ++n) dma(n);
 #pragma unroll
-          for (int q = 0; q < QE; ++q) issue_one(1, 1, q);
+        for (int n = 0; n < SH + NJ; ++n)
+          if (n < nr) rd(n);
+      } else {
+#pragma unroll
+        for (int n = 0; n < QM; ++n) {
+          dma(n);
+          const int i = n / NJ, j = n % NJ;
+          mma16(acc[j / SN][h * SH + i][j % SN], wf[ks][j], xa[ks][i]);
+          if (n < nr) rd(n);
+          __builtin_amdgcn_sched_barrier(0);
         }
-      }
-      vm_barrier<EARLY ? QE : NLD * (NST - 2)>();
-      // `signal`: counted once every wave's earlier stores have completed
-      // (the wait drains every earlier memory operation of the wave, and the
-      // barrier meets all waves)
-      if (signal != nullptr) {
-        if constexpr (NST != 2 || EARLY) vm_barrier<0>();
-        if (threadIdx.x == 0) atomicAdd(signal, 1);
-      }
-      fload(0, 0, 0);
-      for (int kt = 0; kt < nk; kt += NST) {
 #pragma unroll
-        for (int u = 0; u < NST; ++u) iteration(mode, kt + u, u);
+        for (int n = QM; n < SH + NJ; ++n)
+          if (n < nr) rd(n);
       }
-      // the last DMAs (zeros past K) land before the buffers are reused
+    };
+    using std::integral_constant;
+    quarter(integral_constant<int, 0>{}, [&](int) {}, SH + NJ, [&](int n) {
+      if (n < SH) read_a(b, 1, 0, n);
+      else read_w(b, 1, n - SH);
+    });
+    vm_barrier<VM>();
+    tail_w(dkt);
+    tail_a(0, dkt);
+    const __amdgpu_buffer_rsrc_t rw = stage_rsrc(w_base, w_bytes, dkt);
+    const __amdgpu_buffer_rsrc_t ra = stage_rsrc(a_base, a_bytes, dkt);
+    // instruction q of the NWA goes out in slot q * 2 * QM / NWA of Q2 and Q3
+    auto dma_wa = [&](int slot) {
+#pragma unroll
+      for (int q = 0; q < NWA; ++q)
+        if (q * 2 * QM / NWA == slot) {
+          if (q < AH) issue_a(ra, b, 0, q);
+          else issue_w(rw, b, q - AH);
+        }
+    };
+    quarter(integral_constant<int, 1>{}, dma_wa, half ? 0 : SH,
+            [&](int n) { read_a(b, 0, 1, n); });
+    quarter(integral_constant<int, 2>{}, [&](int slot) { dma_wa(QM + slot); }, half ? 0 : SH,
+            [&](int n) { read_a(b, 1, 1, n); });
+    vm_barrier<VM>();
+    tail_a(1, dkt);
+    quarter(integral_constant<int, 3>{},
+            [&](int slot) {
+#pragma unroll
+              for (int q = 0; q < AH; ++q)
+                if (q * QM / AH == slot) issue_a(ra, b, 1, q);
+            },
+            SH + NJ, [&](int n) {
+              if (n < SH) read_a(bn, 0, 0, n);
+              else read_w(bn, 0, n - SH);
+            });
+  };
+  auto k_loop = [&](auto hv) {
+#pragma unroll
+    for (int st = 0; st < NST; ++st) {
+      tail_w(st);
+      tail_a(0, st);
+      tail_a(1, st);
+      const __amdgpu_buffer_rsrc_t rw = stage_rsrc(w_base, w_bytes, st);
+      const __amdgpu_buffer_rsrc_t ra = stage_rsrc(a_base, a_bytes, st);
+#pragma unroll
+      for (int q = 0; q < AH; ++q) issue_a(ra, st, 0, q);
+#pragma unroll
+      for (int q = 0; q < WPW; ++q) issue_w(rw, st, q);
+#pragma unroll
+      for (int q = 0; q < AH; ++q) issue_a(ra, st, 1, q);
+    }
+    // weights and A half 0 of stage 0 have landed
+    if (signal != nullptr) {
+      // counted once every wave's earlier stores have completed (the wait
+      // drains all of the wave's memory operations, the barrier meets all waves)
       vm_barrier<0>();
-    };
-    if (!partial_tile) {
-      if (wave_u < C::NP)
-        k_loop(std::integral_constant<int, 1>{});
-      else
-        k_loop(std::integral_constant<int, 0>{});
+      if (threadIdx.x == 0) atomicAdd(signal, 1);
     } else {
-      if (wave_u < C::NP)
-        k_loop(std::integral_constant<int, 3>{});
-      else
-        k_loop(std::integral_constant<int, 2>{});
+      vm_barrier<NST * NLD - NWA>();
     }
+#pragma unroll
+    for (int i = 0; i < SH; ++i) read_a(0, 0, 0, i);
+#pragma unroll
+    for (int u = 0; u < NJ; ++u) read_w(0, 0, u);
+    acc_fence<C::NB * SM * SN>(&acc[0][0][0]);
+    for (int kt = 0; kt < nk; kt += NST) {
+#pragma unroll
+      for (int u = 0; u < NST; ++u) iteration(hv, kt + u, u);
+    }
+    acc_fence<C::NB * SM * SN>(&acc[0][0][0]);
+    // the last DMAs (zeros past K) land before the buffers are reused
+    vm_barrier<0>();
+  };
+  if (half_only) k_loop(std::true_type{});
+  else k_loop(std::false_type{});
 
-    // Thread indices of the epilogue, taken afresh: address arithmetic on
-    // the ones above would be hoisted before the K loop and kept live through
-    // it, where the accumulators and fragments leave no registers for it, so
-    // the compiler would spill it and reload each value behind a wait for
-    // every outstanding store.
-    const int tid_e = opaque_int((int)threadIdx.x);
-    const int lane_e = tid_e & (kWave - 1);
-    const int wm_e = (tid_e >> 6) / WN, wn_e = (tid_e >> 6) % WN;
-    const int lrow_e = lane_e & 31;
-    // epilogue: lane_e holds row m = .. + lane_e%32, columns n = .. + 8q + 4*(lane_e/32) + [0,4)
-    [[maybe_unused]] const __amdgpu_buffer_rsrc_t out_rsrc = make_rsrc_u(out, g.out_bytes);
-    if constexpr (RESID) {
-      // the residual added to the accumulators, the loads of all of the
-      // lane_e's outputs in flight together
-      f32x4 xv[C::SM][C::SN][4];
+  // Thread indices of the epilogue, taken afresh: address arithmetic on
+  // the ones above would be hoisted before the K loop and kept live through
+  // it, where the accumulators and fragments leave no registers for it, so
+  // the compiler would spill it and reload each value behind a wait for
+  // every outstanding store.
+  const int tid_e = opaque_int((int)threadIdx.x);
+  const int lane_e = tid_e & (kWave - 1);
+  const int wm_e = (tid_e >> 6) / WN, wn_e = (tid_e >> 6) % WN;
+  const int lrow_e = lane_e & 15;
+  // epilogue: lane_e holds row m = .. + lane_e%16, columns n = .. + 4*(lane_e/16) + [0,4)
+  const int ncol_e = (lane_e >> 4) * 4;
+  [[maybe_unused]] const __amdgpu_buffer_rsrc_t out_rsrc = make_rsrc_u(out, g.out_bytes);
+  if constexpr (RESID) {
+    // the residual added to the accumulators, the loads of all of the
+    // lane_e's outputs in flight together
+    f32x4 xv[SM][SN];
 #pragma unroll
-      for (int i = 0; i < C::SM; ++i)
+    for (int i = 0; i < SM; ++i)
 #pragma unroll
-        for (int j = 0; j < C::SN; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int m = row0 + wm_e * C::WTM + i * 32 + lrow_e;
-            const int n = n0 + wn_e * C::WTN + j * 32 + q * 8 + (lane_e >> 5) * 4;
-            xv[i][j][q] = (m < row_end && n < N)
-                              ? *reinterpret_cast<const f32x4*>(res.x + (size_t)m * N + n)
-                              : f32x4{0.f, 0.f, 0.f, 0.f};
-          }
-#pragma unroll
-      for (int i = 0; i < C::SM; ++i)
-#pragma unroll
-        for (int j = 0; j < C::SN; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[0][i][j][q * 4 + v] += xv[i][j][q][v];
-    }
-    if constexpr (GATEUP && OUT_CPOL != 0) {
-      if (!g.halves) {
-        // Device-scope stores of whole lines: the SwiGLU tile goes to LDS
-        // first (free after the K loop; 16-byte chunk c of tile row r at slot
-        // c ^ (r & 15), so the writes of 16 rows at one chunk spread over the
-        // banks), then every lane_e stores 16-byte chunks of whole rows (a wave
-        // instruction covers 4 rows of 256 bytes), so the stores that pass
-        // the L2 are full 128-byte lines rather than 16-byte pieces of 32.
-        static_assert(BN == 128, "16 chunks per staged row");
-        constexpr int ORB = BN * 2;
-#pragma unroll
-        for (int i = 0; i < C::SM; ++i) {
-          const int rr = wm_e * C::WTM + i * 32 + lrow_e;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int ch = (wn_e * C::WTN + q * 8) / 8;
-            bf16x4 o;
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-              o[v] = (bf16)(silu_f(acc[0][i][0][q * 4 + v]) * acc[1][i][0][q * 4 + v]);
-            *reinterpret_cast<bf16x4*>(smem + rr * ORB + ((ch ^ (rr & 15)) * 16) +
-                                       (lane_e >> 5) * 8) = o;
-          }
-        }
-        lds_barrier();
-        constexpr int NCH = BM * (BN / 8);
-        static_assert(NCH % C::NTHR == 0, "whole store rounds");
-#pragma unroll
-        for (int k = 0; k < NCH / C::NTHR; ++k) {
-          const int c = tid_e + k * C::NTHR;
-          const int rr = c / (BN / 8), ch = c % (BN / 8);
-          const int m = row0 + rr, n = n0 + ch * 8;
-          if (m < row_end && n < N) {
-            const bf16x8 o =
-                *reinterpret_cast<const bf16x8*>(smem + rr * ORB + ((ch ^ (rr & 15)) * 16));
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), out_rsrc,
-                                                   (uint32_t)(((size_t)m * N + n) * 2), 0,
-                                                   OUT_CPOL);
-          }
-        }
-        return;
+      for (int j = 0; j < SN; ++j) {
+        const int m = row0 + wm_e * C::WTM + i * 16 + lrow_e;
+        const int n = n0 + wn_e * C::WTN + j * 16 + ncol_e;
+        xv[i][j] = (m < row_end && n < N)
+                       ? *reinterpret_cast<const f32x4*>(res.x + (size_t)m * N + n)
+                       : f32x4{0.f, 0.f, 0.f, 0.f};
       }
-    }
-    if constexpr (GATEUP) {
-      if (g.halves) {
-        // The BM x 2*BN output tile (slice b at columns ntile*2*BN + b*BN + ..)
-        // goes to LDS first (the stage buffers are free after the K loop;
-        // 16-byte chunk c of tile row r at slot c ^ (r & 31)), then every lane_e
-        // stores 16-byte chunks of whole rows, so a wave instruction writes 2
-        // full rows (8 whole 128-byte lines) instead of 32 rows x 16 bytes.
-        static_assert(C::SN == 1 && BN == 128, "32 chunks per staged row");
-        constexpr int ORB = 2 * BN * 2;                 // bytes per staged row
-        constexpr int RCH = 2 * BN / 8;                 // 16-byte chunks per row
-        static_assert(BM * ORB <= NST * C::STAGE, "staged tile fits the stage buffers");
 #pragma unroll
-        for (int i = 0; i < C::SM; ++i) {
-          const int rr = wm_e * C::WTM + i * 32 + lrow_e;
+    for (int i = 0; i < SM; ++i)
 #pragma unroll
-          for (int b = 0; b < 2; ++b)
+      for (int j = 0; j < SN; ++j)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const int ch = b * (BN / 8) + (wn_e * C::WTN + q * 8) / 8;
-              bf16x4 o;
+        for (int v = 0; v < 4; ++v) acc[0][i][j][v] += xv[i][j][v];
+  }
+  if constexpr (GATEUP && OUT_CPOL != 0) {
+    if (!g.halves) {
+      // Device-scope stores of whole lines: the SwiGLU tile goes to LDS
+      // first (free after the K loop; 16-byte chunk c of tile row r at slot
+      // c ^ (r % OCH), so the writes of 16 rows at one chunk spread over the
+      // banks), then every lane_e stores 16-byte chunks of whole rows, so the
+      // stores that pass the L2 are full 128-byte lines rather than 16-byte
+      // pieces of 32.
+      constexpr int OCH = BN / 8, ORB = BN * 2;  // chunks and bytes of a staged row
 #pragma unroll
-              for (int v = 0; v < 4; ++v) o[v] = (bf16)acc[b][i][0][q * 4 + v];
-              *reinterpret_cast<bf16x4*>(smem + rr * ORB + ((ch ^ (rr & 31)) * 16) +
-                                         (lane_e >> 5) * 8) = o;
-            }
-        }
-        lds_barrier();
-        // thread tid_e stores chunk tid_e % RCH of rows tid_e / RCH + k * RPR
-        constexpr int RPR = C::NTHR / RCH;  // rows per store round
-        static_assert(C::NTHR % RCH == 0 && BM % (2 * RPR) == 0 && 32 % RPR == 0,
-                      "store rounds");
-        const int ch = tid_e % RCH, r0 = tid_e / RCH;
-        const int n = ntile * 2 * BN + ch * 8;
-        if (n < N) {
-          // rows r0 + k*RPR take 32 / RPR values of r & 31, so as many LDS
-          // slot offsets serve all rounds
-          constexpr int NV = 32 / RPR;
-          int slot[NV];
+      for (int i = 0; i < SM; ++i) {
+        const int rr = wm_e * C::WTM + i * 16 + lrow_e;
 #pragma unroll
-          for (int v = 0; v < NV; ++v) slot[v] = (ch ^ ((r0 + v * RPR) & 31)) * 16;
-          const unsigned char* src = smem + r0 * ORB;
-          bf16* dst = out + (size_t)(row0 + r0) * N + n;
-          const int nr = row_end - row0 - r0;  // rows of this thread's column still valid
-#pragma unroll
-          for (int k = 0; k < BM / RPR; ++k) {
-            if (k * RPR < nr)
-              *reinterpret_cast<bf16x8*>(dst + (size_t)k * RPR * N) =
-                  *reinterpret_cast<const bf16x8*>(src + k * RPR * ORB + slot[k % NV]);
-          }
-        }
-        return;
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < C::SM; ++i) {
-      const int m = row0 + wm_e * C::WTM + i * 32 + lrow_e;
-      if (m >= row_end) continue;
-#pragma unroll
-      for (int j = 0; j < C::SN; ++j) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int n = n0 + wn_e * C::WTN + j * 32 + q * 8 + (lane_e >> 5) * 4;
-          if (n >= N) continue;
-          float val[4];
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            val[v] = acc[0][i][j][q * 4 + v];
-            if constexpr (GATEUP) val[v] = silu_f(val[v]) * acc[C::NB - 1][i][j][q * 4 + v];
-          }
-          if constexpr (RESID) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) val[v] *= res.scale;
-          }
+        for (int j = 0; j < SN; ++j) {
+          const int ch = (wn_e * C::WTN + j * 16 + ncol_e) / 8;
           bf16x4 o;
 #pragma unroll
-          for (int v = 0; v < 4; ++v) o[v] = (bf16)val[v];
-          if constexpr (OUT_CPOL != 0)
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), out_rsrc,
-                                                  (uint32_t)(((size_t)m * N + n) * 2), 0,
-                                                  OUT_CPOL);
-          else
-            *reinterpret_cast<bf16x4*>(out + (size_t)m * N + n) = o;
+          for (int v = 0; v < 4; ++v)
+            o[v] = (bf16)(silu_f(acc[0][i][j][v]) * acc[1][i][j][v]);
+          *reinterpret_cast<bf16x4*>(smem + rr * ORB + ((ch ^ (rr % OCH)) * 16) +
+                                     (ncol_e & 4) * 2) = o;
         }
       }
+      lds_barrier();
+      constexpr int NCH = BM * OCH;
+      static_assert(NCH % C::NTHR == 0, "whole store rounds");
+#pragma unroll
+      for (int k = 0; k < NCH / C::NTHR; ++k) {
+        const int c = tid_e + k * C::NTHR;
+        const int rr = c / OCH, ch = c % OCH;
+        const int m = row0 + rr, n = n0 + ch * 8;
+        if (m < row_end && n < N) {
+          const bf16x8 o =
+              *reinterpret_cast<const bf16x8*>(smem + rr * ORB + ((ch ^ (rr % OCH)) * 16));
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), out_rsrc,
+                                                 (uint32_t)(((size_t)m * N + n) * 2), 0,
+                                                 OUT_CPOL);
+        }
+      }
+      return;
+    }
+  }
+  if constexpr (GATEUP) {
+    if (g.halves) {
+      // The BM x 2*BN output tile (slice b at columns ntile*2*BN + b*BN + ..)
+      // goes to LDS first (the stage buffers are free after the K loop;
+      // 16-byte chunk c of tile row r at slot c ^ (r % RCH)), then every lane_e
+      // stores 16-byte chunks of whole rows, so a wave instruction writes
+      // whole 128-byte lines instead of 16 rows x 32 bytes.
+      constexpr int ORB = 2 * BN * 2;                 // bytes per staged row
+      constexpr int RCH = 2 * BN / 8;                 // 16-byte chunks per row
+      static_assert(BM * ORB <= NST * C::STAGE, "staged tile fits the stage buffers");
+#pragma unroll
+      for (int i = 0; i < SM; ++i) {
+        const int rr = wm_e * C::WTM + i * 16 + lrow_e;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int j = 0; j < SN; ++j) {
+            const int ch = b * (BN / 8) + (wn_e * C::WTN + j * 16 + ncol_e) / 8;
+            bf16x4 o;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) o[v] = (bf16)acc[b][i][j][v];
+            *reinterpret_cast<bf16x4*>(smem + rr * ORB + ((ch ^ (rr % RCH)) * 16) +
+                                       (ncol_e & 4) * 2) = o;
+          }
+      }
+      lds_barrier();
+      // thread tid_e stores chunk tid_e % RCH of rows tid_e / RCH + k * RPR
+      constexpr int RPR = C::NTHR / RCH;  // rows per store round
+      static_assert(C::NTHR % RCH == 0 && BM % RPR == 0 && RCH % RPR == 0, "store rounds");
+      const int ch = tid_e % RCH, r0 = tid_e / RCH;
+      const int n = ntile * 2 * BN + ch * 8;
+      if (n < N) {
+        // rows r0 + k*RPR take RCH / RPR values modulo RCH, so as many LDS
+        // slot offsets serve all rounds
+        constexpr int NV = RCH / RPR;
+        int slot[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) slot[v] = (ch ^ ((r0 + v * RPR) % RCH)) * 16;
+        const unsigned char* src = smem + r0 * ORB;
+        bf16* dst = out + (size_t)(row0 + r0) * N + n;
+        const int nr = row_end - row0 - r0;  // rows of this thread's column still valid
+#pragma unroll
+        for (int k = 0; k < BM / RPR; ++k) {
+          if (k * RPR < nr)
+            *reinterpret_cast<bf16x8*>(dst + (size_t)k * RPR * N) =
+                *reinterpret_cast<const bf16x8*>(src + k * RPR * ORB + slot[k % NV]);
+        }
+      }
+      return;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < SM; ++i) {
+    const int m = row0 + wm_e * C::WTM + i * 16 + lrow_e;
+    if (m >= row_end) continue;
+#pragma unroll
+    for (int j = 0; j < SN; ++j) {
+      const int n = n0 + wn_e * C::WTN + j * 16 + ncol_e;
+      if (n >= N) continue;
+      bf16x4 o;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float val = acc[0][i][j][v];
+        if constexpr (GATEUP) val = silu_f(val) * acc[C::NB - 1][i][j][v];
+        if constexpr (RESID) val *= res.scale;
+        o[v] = (bf16)val;
+      }
+      if constexpr (OUT_CPOL != 0)
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), out_rsrc,
+                                              (uint32_t)(((size_t)m * N + n) * 2), 0, OUT_CPOL);
+      else
+        *reinterpret_cast<bf16x4*>(out + (size_t)m * N + n) = o;
     }
   }
 }
@@ -815,18 +809,18 @@ __device__ __forceinline__ void tile_coords(int t, int ntn, int m_tiles, int& mt
   }
 }
 
-template <int BM, int BN, int WM, int WN, bool GATEUP, int BK, int NST, int PW, int GM,
-          int PERSIST, bool RESID = false>
+template <int BM, int BN, int WM, int WN, bool GATEUP, int NST, int GM, int PERSIST,
+          bool RESID = false>
 __global__ __launch_bounds__(WM* WN* kWave) __attribute__((amdgpu_waves_per_eu(1, 2)))
 void grouped_gemm_dma(const bf16* __restrict__ A, const int32_t* __restrict__ gather, int kdiv,
                       int a_rows, const int32_t* __restrict__ offsets, int E, int rows,
                       const bf16* __restrict__ B0, const bf16* __restrict__ B1, int N, int K,
                       bf16* __restrict__ out, int n_tiles_n, int n_tiles, GemmResid res) {
-  using C = DmaCfg<BM, BN, WM, WN, GATEUP, BK, NST, PW>;
+  using C = DmaCfg<BM, BN, WM, WN, GATEUP, NST>;
   __shared__ __align__(1024) unsigned char smem[NST * C::STAGE];
   const GemmArgs g{A, gather, kdiv, a_rows, B0, B1, N, K, out, 0u, res, false};
   auto run_tile = [&](const int e, const int row0, const int row_end, const int ntile) {
-    gemm_tile<BM, BN, WM, WN, GATEUP, BK, NST, PW, RESID, 0>(smem, g, e, row0, row_end, ntile);
+    gemm_tile<BM, BN, WM, WN, GATEUP, NST, RESID, 0>(smem, g, e, row0, row_end, ntile);
   };
 
   // M-tiles that hold rows (persistent form: the tile list is split over
@@ -906,11 +900,6 @@ void grouped_gemm_dma(const bf16* __restrict__ A, const int32_t* __restrict__ ga
 // zeroed before the launch (by the index pass).
 constexpr int kReadyPollLimit = 1 << 20;  // about a second of polling
 
-// waves of the fused FFN that issue the DMA: all 8 (each its share of a
-// stage, ahead of its MFMAs) measured 2-5% faster than one per SIMD
-#ifndef FOE_FUSED_PW
-#define FOE_FUSED_PW 8
-#endif
 // M-tiles per group of the fused FFN's tile order (a group's gate/up tiles
 // are walked N-tile by N-tile)
 #ifndef FOE_FUSED_GM
@@ -950,7 +939,7 @@ struct FusedLists {
   }
 };
 
-template <int BM, int BN, int WM, int WN, int BK, int NST, int PW, int GM>
+template <int BM, int BN, int WM, int WN, int NST, int GM>
 __global__ __launch_bounds__(WM* WN* kWave) __attribute__((amdgpu_waves_per_eu(1, 2)))
 void ffn_fused_dma(const bf16* __restrict__ A, const int32_t* __restrict__ gather, int kdiv,
                    int a_rows, const int32_t* __restrict__ offsets, int E, int rows,
@@ -960,7 +949,7 @@ void ffn_fused_dma(const bf16* __restrict__ A, const int32_t* __restrict__ gathe
   // one tile shape for both GEMMs: BM rows x (BN gate + BN up) columns, or
   // BM rows x 2*BN down columns read as two BN-row slices of W_d (the same
   // operand loads, LDS layout and MFMA sequence; only the epilogue differs)
-  using C = DmaCfg<BM, BN, WM, WN, true, BK, NST, PW>;
+  using C = DmaCfg<BM, BN, WM, WN, true, NST>;
   __shared__ __align__(1024) unsigned char smem[NST * C::STAGE];
   __shared__ int s_item[2];  // alternate slots: a slot is rewritten one barrier after it is read
   __shared__ int s_tab[3 * kTileTab];
@@ -1070,7 +1059,7 @@ void ffn_fused_dma(const bf16* __restrict__ A, const int32_t* __restrict__ gathe
                                        (uint32_t)rows * F * 2u, GemmResid{}, false}
                             : GemmArgs{h, nullptr, 1, rows, wd, nullptr, d, F, y,
                                        (uint32_t)rows * d * 2u, GemmResid{}, true};
-      gemm_tile<BM, BN, WM, WN, true, BK, NST, PW, false, kScDevice>(
+      gemm_tile<BM, BN, WM, WN, true, NST, false, kScDevice>(
           smem, g, e, row0, row_end, nt, gu && pending >= 0 ? &ready[pending] : nullptr);
       if (gu) pending = mt;
     }
@@ -1479,7 +1468,7 @@ int device_cus() {
   return n / 8 * 8;
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int NST, int PW, int GM, int PERSIST, bool GATEUP,
+template <int BM, int BN, int WM, int WN, int NST, int GM, int PERSIST, bool GATEUP,
           bool RESID = false>
 void launch_gemm_dma(const bf16* A, const int32_t* gather, int kdiv, int a_rows,
                      const int32_t* offsets, int E, int rows, const bf16* B0, const bf16* B1,
@@ -1495,16 +1484,16 @@ void launch_gemm_dma(const bf16* A, const int32_t* gather, int kdiv, int a_rows,
   }
   dim3 grid((unsigned)nb);
   ProfileScope ps(name, s);
-  FOE_LAUNCH((grouped_gemm_dma<BM, BN, WM, WN, GATEUP, BK, NST, PW, GM, PERSIST, RESID>),
+  FOE_LAUNCH((grouped_gemm_dma<BM, BN, WM, WN, GATEUP, NST, GM, PERSIST, RESID>),
              grid, dim3(WM * WN * kWave), 0, s, A, gather, kdiv, a_rows, offsets, E, rows, B0, B1,
              N, K, out, ntn, (int)n_tiles, res);
 }
 
-template <int BM, int BN, int WM, int WN, int BK, int NST, int PW, int GM, int PERSIST>
+template <int BM, int BN, int WM, int WN, int NST, int GM, int PERSIST>
 struct DmaLaunch {
   template <bool GATEUP, bool RESID = false, typename... Args>
   static void run(Args... args) {
-    launch_gemm_dma<BM, BN, WM, WN, BK, NST, PW, GM, PERSIST, GATEUP, RESID>(args...);
+    launch_gemm_dma<BM, BN, WM, WN, NST, GM, PERSIST, GATEUP, RESID>(args...);
   }
 };
 
@@ -1577,7 +1566,7 @@ hipError_t launch_expert_ffn_fused(int E, int d, int F, int rows, const void* A,
   if (rows == 0) return hipSuccess;
   static const int cus = device_cus();
   ProfileScope ps("ffn_fused", s);
-  FOE_LAUNCH((ffn_fused_dma<256, 128, 2, 4, 64, 2, FOE_FUSED_PW, FOE_FUSED_GM>), dim3(cus),
+  FOE_LAUNCH((ffn_fused_dma<256, 128, 2, 4, 2, FOE_FUSED_GM>), dim3(cus),
              dim3(8 * kWave), 0, s,
              static_cast<const bf16*>(A), gather, kdiv, a_rows, offsets, E, rows,
              static_cast<const bf16*>(w_gate), static_cast<const bf16*>(w_up),
