@@ -36,14 +36,25 @@
 #ifndef FOE_DMA_SEG
 #define FOE_DMA_SEG 256, 256, 2, 4, 2, 4, 2
 #endif
-// plain GEMM with the residual epilogue (few M rows: 128 x 256 tiles, or
-// 128 x 128 when the larger tiles would leave compute units idle); one tile
-// per CU walks all of K, so a third LDS stage keeps more loads in flight
+// plain GEMM with the residual epilogue (few M rows)
 #ifndef FOE_DMA_RES
 #define FOE_DMA_RES 128, 256, 2, 4, 3, 4, 1
 #endif
-#ifndef FOE_DMA_RES_SMALL
-#define FOE_DMA_RES_SMALL 128, 128, 2, 4, 3, 4, 1
+// Smaller tiles of both, for products with few large tiles.  Each CU then runs
+// at most one tile, a walk down K that waits for its loads, so the tile is the
+// largest that still leaves no more tiles than CUs and more stages keep the
+// loads in flight: 128 x 128 where the larger tiles would leave CUs idle, and
+// 64 x 128 where even those tiles fit the chip at once.  q/k/v product of 8
+// groups, 1000 rows, N 288, K 768: 21.6 us with 64 tiles of 256 x 256, 11.4
+// with 192 of 128 x 128, 15.2 with 384 of 64 x 128; output projection of 1000
+// rows, N 768, K 768: 12.6 with 48 tiles of 128 x 128, 11.3 with 96 of 64 x 128
+// (300 rows: 12.8 and 9.8).  At 1500 rows, N 2048, K 2048 the output
+// projection has 192 tiles of 128 x 128 (24 us) against 384 of 64 x 128 (31).
+#ifndef FOE_DMA_SMALL
+#define FOE_DMA_SMALL 128, 128, 2, 4, 3, 4
+#endif
+#ifndef FOE_DMA_TINY
+#define FOE_DMA_TINY 64, 128, 1, 4, 4, 4
 #endif
 // few rows per expert (decode): LDS-staged weight stream with NS stages, K
 // walk rotated per workgroup, and (block decode form) pair lists built in the
@@ -1497,6 +1508,19 @@ struct DmaLaunch {
   }
 };
 
+// Calls f with the tile size (0 = 64 x 128, 1 = 128 x 128, 2 = bm x bn) of a
+// plain product of E equal segments (see FOE_DMA_SMALL).
+template <typename F>
+void pick_tile(int E, int rows, int N, int bm, int bn, F&& f) {
+  static const int cus = device_cus();
+  auto tiles = [&](int m, int n) {
+    return (long long)E * ceil_div(rows, (long long)m * E) * ceil_div(N, n);
+  };
+  if (tiles(64, 128) <= cus) f(std::integral_constant<int, 0>{});
+  else if (tiles(bm, bn) < cus) f(std::integral_constant<int, 1>{});
+  else f(std::integral_constant<int, 2>{});
+}
+
 }  // namespace
 
 size_t ffn_scratch_bytes(foe_dtype dt, int rows, int F) {
@@ -1615,9 +1639,17 @@ hipError_t launch_grouped_gemm(const void* A, const int32_t* offsets, int E, int
                                const void* W, int N, int K, void* out, hipStream_t s,
                                const char* name) {
   if (rows == 0) return hipSuccess;
-  DmaLaunch<FOE_DMA_SEG>::run<false>(static_cast<const bf16*>(A), (const int32_t*)nullptr, 1, rows,
-                                    offsets, E, rows, static_cast<const bf16*>(W),
-                                    (const bf16*)nullptr, N, K, static_cast<bf16*>(out), s, name);
+  pick_tile(E, rows, N, 256, 256, [&](auto size) {
+    auto go = [&](auto cfg) {
+      decltype(cfg)::template run<false>(static_cast<const bf16*>(A), (const int32_t*)nullptr, 1,
+                                         rows, offsets, E, rows, static_cast<const bf16*>(W),
+                                         (const bf16*)nullptr, N, K, static_cast<bf16*>(out), s,
+                                         name);
+    };
+    if constexpr (size.value == 0) go(DmaLaunch<FOE_DMA_TINY, 2>{});
+    else if constexpr (size.value == 1) go(DmaLaunch<FOE_DMA_SMALL, 2>{});
+    else go(DmaLaunch<FOE_DMA_SEG>{});
+  });
   return hipGetLastError();
 }
 
@@ -1628,17 +1660,17 @@ hipError_t launch_gemm_resid(const void* A, const int32_t* offsets, int rows, co
   GemmResid res;
   res.x = x;
   res.scale = scale;
-  static const int cus = device_cus();
-  if ((long long)ceil_div(rows, 128) * ceil_div(N, 256) < cus)
-    DmaLaunch<FOE_DMA_RES_SMALL>::run<false, true>(
-        static_cast<const bf16*>(A), (const int32_t*)nullptr, 1, rows, offsets, 1, rows,
-        static_cast<const bf16*>(W), (const bf16*)nullptr, N, K, static_cast<bf16*>(out), s, name,
-        res);
-  else
-    DmaLaunch<FOE_DMA_RES>::run<false, true>(
-        static_cast<const bf16*>(A), (const int32_t*)nullptr, 1, rows, offsets, 1, rows,
-        static_cast<const bf16*>(W), (const bf16*)nullptr, N, K, static_cast<bf16*>(out), s, name,
-        res);
+  pick_tile(1, rows, N, 128, 256, [&](auto size) {
+    auto go = [&](auto cfg) {
+      decltype(cfg)::template run<false, true>(
+          static_cast<const bf16*>(A), (const int32_t*)nullptr, 1, rows, offsets, 1, rows,
+          static_cast<const bf16*>(W), (const bf16*)nullptr, N, K, static_cast<bf16*>(out), s,
+          name, res);
+    };
+    if constexpr (size.value == 0) go(DmaLaunch<FOE_DMA_TINY, 1>{});
+    else if constexpr (size.value == 1) go(DmaLaunch<FOE_DMA_SMALL, 1>{});
+    else go(DmaLaunch<FOE_DMA_RES>{});
+  });
   return hipGetLastError();
 }
 
