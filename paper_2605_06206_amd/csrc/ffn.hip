@@ -18,7 +18,7 @@
 // host sync is needed.
 //
 // bf16, few rows per expert (decode, weight-streaming bound): see
-// ffn_stream_bf16.  fp32: plain FMA kernels (small shapes only).
+// ffn_stream_bf16.  fp32: the same tiles with fp32 MFMAs.
 #include <type_traits>
 
 #include "lds_dma.hpp"
@@ -55,6 +55,13 @@
 #endif
 #ifndef FOE_DMA_TINY
 #define FOE_DMA_TINY 64, 128, 1, 4, 4, 4
+#endif
+// fp32 expert FFN: gate/up and down tiles (two workgroups per CU)
+#ifndef FOE_F32_GU
+#define FOE_F32_GU 64, 32, 2, 2, 4, 4, 1
+#endif
+#ifndef FOE_F32_DN
+#define FOE_F32_DN 64, 64, 2, 2, 4, 4, 1
 #endif
 // few rows per expert (decode): LDS-staged weight stream with NS stages, K
 // walk rotated per workgroup, and (block decode form) pair lists built in the
@@ -275,25 +282,25 @@ __device__ __forceinline__ int src_row(const int32_t* __restrict__ gather, int k
 // explicit vmcnt waits (the compiler does not see them; the kernel issues no
 // other global loads inside the main loop and uses M0 nowhere else).
 //
-// LDS layout of a tile: rows of 64 bf16 (no padding), the 16-byte chunk c of
-// row r stored in slot c ^ swz_tile(r).  A fragment read takes one chunk of 16
+// LDS layout of a tile: rows of 128 bytes (64 bf16 or 32 fp32, no padding), the
+// 16-byte chunk c of row r stored in slot c ^ swz_tile(r).  A fragment read takes one chunk of 16
 // rows, two rows to a 256-byte bank line, so the eight rows of each half need
 // eight different slots.  Since a DMA instruction writes 1 KiB contiguously,
 // the swizzle is applied on the load side: the lane that lands in slot s of
 // row r fetches chunk s ^ swz_tile(r).
 __device__ __forceinline__ int swz_tile(int r) { return (r >> 1) & 7; }
 
-template <int BM, int BN, int WM, int WN, bool GATEUP, int NST>
+template <typename T, int BM, int BN, int WM, int WN, bool GATEUP, int NST>
 struct DmaCfg {
-  static constexpr int BK = 64;            // K columns per stage: whole 128-byte lines
+  static constexpr int RB = 128;           // bytes per tile row: whole cache lines
+  static constexpr int BK = RB / (int)sizeof(T);  // K columns per stage
   static constexpr int NW = WM * WN, NTHR = NW * kWave;
   static constexpr int WTM = BM / WM, WTN = BN / WN;
   static constexpr int SM = WTM / 16, SN = WTN / 16;  // 16-row / 16-column sub-tiles
   static constexpr int NB = GATEUP ? 2 : 1;
-  static constexpr int NJ = NB * SN;       // weight fragments of a k32 step
+  static constexpr int NJ = NB * SN;       // weight fragments of a half stage
   static constexpr int SH = SM / 2;        // A fragments of a row half
-  static constexpr int RB = BK * 2;        // bytes per tile row
-  static constexpr int CPR = BK / 8;       // 16-byte chunks per row
+  static constexpr int CPR = RB / 16;      // 16-byte chunks per row
   static constexpr int RPI = 1024 / RB;    // rows per DMA instruction
   static constexpr int A_INS = BM / RPI, B_INS = BN / RPI;  // DMA instructions per tile
   // DMA instructions per wave and stage: weights, and each row half of A
@@ -309,24 +316,46 @@ struct DmaCfg {
   static_assert(NST * STAGE <= 160 * 1024, "LDS capacity");
 };
 
-// acc += w x^T on v_mfma_f32_16x16x32_bf16, the accumulator fixed in AGPRs.
-// (Through the builtin the register allocator gives each result other
+// A 16-byte fragment: 8 bf16 or 4 fp32 of one row.
+template <typename T> using Frag = T __attribute__((ext_vector_type(16 / sizeof(T))));
+
+// acc[j] += w[j] x^T for the NJ weight fragments of one A fragment, step n of
+// NJ (each step the same number of MFMAs), the accumulators fixed in AGPRs.
+// bf16: 16 rows x 32 k, v_mfma_f32_16x16x32_bf16, one per weight fragment.
+// fp32: 16 rows x 16 k, four v_mfma_f32_16x16x4_f32 per weight fragment (the
+// s-th takes element s of every lane's 16 bytes on both operands; fp32
+// products and sums), one statement per step so that an accumulator's
+// dependent MFMAs stay apart.
+// (Through the builtins the register allocator gives each result other
 // registers than its addend and spills around 60 of them inside the K loop.)
 // The compiler does not see an MFMA here: acc_fence() separates the
 // accumulators' first write and last read from the MFMAs by more wait states
-// than the instruction needs; inside the loop an accumulator returns after at
-// least three other MFMAs.
-__device__ __forceinline__ void mma16(f32x4& acc, bf16x8 w, bf16x8 x) {
-  asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
+// than the instructions need; inside the loop an accumulator returns after at
+// least one other MFMA.
+template <int SN, int NJ, typename Acc>
+__device__ __forceinline__ void mma_step(Acc& acc, int i, int n, const bf16x8 (&w)[NJ], bf16x8 x) {
+  asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
+      : "+a"(acc[n / SN][i][n % SN])
+      : "v"(w[n]), "v"(x));
+}
+template <int SN, int NJ, typename Acc>
+__device__ __forceinline__ void mma_step(Acc& acc, int i, int n, const f32x4 (&w)[NJ], f32x4 x) {
+  static_assert(NJ == 2, "two weight fragments");
+  asm("v_mfma_f32_16x16x4_f32 %0, %2, %4, %0\n\t"
+      "v_mfma_f32_16x16x4_f32 %1, %3, %4, %1\n\t"
+      "v_mfma_f32_16x16x4_f32 %0, %5, %7, %0\n\t"
+      "v_mfma_f32_16x16x4_f32 %1, %6, %7, %1"
+      : "+a"(acc[0][i][0]), "+a"(acc[1 / SN][i][1 % SN])
+      : "v"(w[0][2 * n]), "v"(w[1][2 * n]), "v"(x[2 * n]), "v"(w[0][2 * n + 1]),
+        "v"(w[1][2 * n + 1]), "v"(x[2 * n + 1]));
 }
 template <int N>
 __device__ __forceinline__ void acc_fence(f32x4* a) {
-  static_assert(N % 8 == 0, "eight accumulators per statement");
+  static_assert(N % 4 == 0, "four accumulators per statement");
 #pragma unroll
-  for (int i = 0; i < N; i += 8)
+  for (int i = 0; i < N; i += 4)
     asm volatile("s_nop 15\n\ts_nop 15"
-                 : "+a"(a[i]), "+a"(a[i + 1]), "+a"(a[i + 2]), "+a"(a[i + 3]), "+a"(a[i + 4]),
-                   "+a"(a[i + 5]), "+a"(a[i + 6]), "+a"(a[i + 7]));
+                 : "+a"(a[i]), "+a"(a[i + 1]), "+a"(a[i + 2]), "+a"(a[i + 3]));
 }
 
 // Residual epilogue of the plain (non gate/up) form: the output becomes
@@ -340,16 +369,17 @@ struct GemmResid {
 // kdiv from a_rows source rows), one or two [E, N, K] weight stacks, the
 // output [rows, N] (out_bytes = its size, for device-scope stores) and the
 // residual epilogue.
+template <typename T>
 struct GemmArgs {
-  const bf16* A;
+  const T* A;
   const int32_t* gather;
   int kdiv;
   int a_rows;
-  const bf16* B0;
-  const bf16* B1;
+  const T* B0;
+  const T* B1;
   int N;
   int K;
-  bf16* out;
+  T* out;
   uint32_t out_bytes;
   GemmResid res;
   // two-matrix tile shape (GATEUP) used for a plain product: B1 is ignored,
@@ -366,7 +396,8 @@ struct GemmArgs {
 // that other XCDs can read the tile once the stores have completed).  The
 // two-slice form (GemmArgs::halves) always stores as usual, staged through LDS.
 //
-// Stage kt (64 K columns) lives in LDS buffer kt % NST.  What bounds the loop
+// Stage kt (64 K columns; 32 in fp32, where the steps below are half as wide)
+// lives in LDS buffer kt % NST.  What bounds the loop
 // is the delivery of the operands: a 256 x 256 tile needs 64 KiB per stage,
 // which takes longer to arrive than the stage's MFMAs take, so the loads must
 // be in flight well over one iteration ahead.  With two stage buffers that
@@ -394,25 +425,29 @@ struct GemmArgs {
 // the power limit allows (1.85 GHz) and the tiles' beginnings and ends.
 // 16x16x32 MFMAs: a register-only loop reaches 2.04 PFLOP/s with them and 1.86
 // with 32x32x16 ones.
-template <int BM, int BN, int WM, int WN, bool GATEUP, int NST, bool RESID, int OUT_CPOL>
-__device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs& g, const int e_,
+template <typename T, int BM, int BN, int WM, int WN, bool GATEUP, int NST, bool RESID,
+          int OUT_CPOL>
+__device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs<T>& g, const int e_,
                                           const int row0_, const int row_end_, const int ntile_,
                                           int32_t* signal = nullptr) {
   static_assert(!(RESID && GATEUP), "residual epilogue on the plain form only");
-  using C = DmaCfg<BM, BN, WM, WN, GATEUP, NST>;
+  static_assert(sizeof(T) == 2 || OUT_CPOL == 0, "fp32 stores as usual");
+  using C = DmaCfg<T, BM, BN, WM, WN, GATEUP, NST>;
   constexpr int BK = C::BK, WPW = C::WPW, AH = C::AH, NLD = C::NLD;
+  constexpr uint32_t ES = sizeof(T);
+  constexpr bool BF16 = ES == 2;
   // the tile is the same for the whole workgroup: its coordinates (read from
   // LDS) and what follows from them stay in scalar registers
   const int e = __builtin_amdgcn_readfirstlane(e_);
   const int row0 = __builtin_amdgcn_readfirstlane(row0_);
   const int row_end = __builtin_amdgcn_readfirstlane(row_end_);
   const int ntile = __builtin_amdgcn_readfirstlane(ntile_);
-  const bf16* __restrict__ A = g.A;
+  const T* __restrict__ A = g.A;
   const int32_t* __restrict__ gather = g.gather;
   const int kdiv = g.kdiv, a_rows = g.a_rows, N = g.N, K = g.K;
-  const bf16* __restrict__ B0 = g.B0;
-  const bf16* __restrict__ B1 = g.B1;
-  bf16* __restrict__ out = g.out;
+  const T* __restrict__ B0 = g.B0;
+  const T* __restrict__ B1 = g.B1;
+  T* __restrict__ out = g.out;
   const GemmResid& res = g.res;
 
   // opaque: what follows from the lane is formed anew for every tile instead
@@ -428,23 +463,23 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs& g
   // lane l lands in row l / CPR, slot l % CPR and fetches chunk
   // (l % CPR) ^ swz_tile(row).
   const int rl = lane / C::CPR, cl = lane % C::CPR;
-  auto kcol = [&](int ii) { return (cl ^ swz_tile(ii * C::RPI + rl)) * 8; };
+  auto kcol = [&](int ii) { return (cl ^ swz_tile(ii * C::RPI + rl)) * (16 / (int)ES); };
   // weights: slice ws, its instruction wi0; a slice past N is empty
   const int wp = wave_u * WPW, ws = wp / C::B_INS, wi0 = wp % C::B_INS;
   int wrow0 = n0;  // first row of the slice
-  const bf16* wmat = B0;
+  const T* wmat = B0;
   if constexpr (GATEUP) {
     if (g.halves) wrow0 = ntile * 2 * BN + ws * BN;
     else if (ws == 1) wmat = B1;
   }
   wrow0 = min(wrow0, N);
   const uint64_t w_base = (uint64_t)(uintptr_t)(wmat + ((size_t)e * N + wrow0) * K);
-  const uint32_t w_bytes = (uint32_t)min(BN, N - wrow0) * K * 2u;
+  const uint32_t w_bytes = (uint32_t)min(BN, N - wrow0) * K * ES;
   // A: the tile's rows, or the whole source when gathering
   const uint64_t a_base =
       (uint64_t)(uintptr_t)(gather == nullptr ? A + (size_t)row0 * K : A);
-  const uint32_t a_bytes = gather == nullptr ? (uint32_t)min(BM, row_end - row0) * K * 2u
-                                             : (uint32_t)a_rows * K * 2u;
+  const uint32_t a_bytes = gather == nullptr ? (uint32_t)min(BM, row_end - row0) * K * ES
+                                             : (uint32_t)a_rows * K * ES;
   // instruction q of row half h: rows of one 16-row run after another of the
   // wave rows' halves
   auto a_ins = [&](int h, int q) {
@@ -455,17 +490,17 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs& g
   uint32_t off_w[WPW], off_a[2][AH];
 #pragma unroll
   for (int q = 0; q < WPW; ++q)
-    off_w[q] = ((uint32_t)((wi0 + q) * C::RPI + rl) * K + kcol(wi0 + q)) * 2u;
+    off_w[q] = ((uint32_t)((wi0 + q) * C::RPI + rl) * K + kcol(wi0 + q)) * ES;
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int q = 0; q < AH; ++q) {
       const int ii = a_ins(h, q), r = ii * C::RPI + rl;
       if (gather == nullptr) {
-        off_a[h][q] = ((uint32_t)r * K + kcol(ii)) * 2u;
+        off_a[h][q] = ((uint32_t)r * K + kcol(ii)) * ES;
       } else {
         const int s = (row0 + r < row_end) ? src_row(gather, kdiv, row0 + r, a_rows) : -1;
-        off_a[h][q] = s < 0 ? kOob : ((uint32_t)s * K + kcol(ii)) * 2u;
+        off_a[h][q] = s < 0 ? kOob : ((uint32_t)s * K + kcol(ii)) * ES;
       }
     }
   const uint32_t smem_base = lds_addr(smem);
@@ -480,7 +515,7 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs& g
   // instruction that wrote it would need wait states before the loads, which
   // the compiler cannot see)
   auto stage_rsrc = [&](uint64_t base, uint32_t bytes, int kt) {
-    const int k2 = kt * BK * 2;
+    const int k2 = kt * C::RB;
     return make_rsrc_u(reinterpret_cast<const void*>((uintptr_t)(base + (uint32_t)k2)),
                        (uint32_t)max((int)bytes - k2, 0));
   };
@@ -528,13 +563,13 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs& g
       oa[b][ks] = opaque_int((wm * C::WTM + lrow) * C::RB + x);
       ob[b][ks] = opaque_int(C::A_BYTES + (wn * C::WTN + lrow) * C::RB + x);
     }
-  bf16x8 xa[2][SH];  // A fragments of this and of the next quarter
-  bf16x8 wf[2][NJ];  // weight fragments of k32 step 0 and 1
+  Frag<T> xa[2][SH];  // A fragments of this and of the next quarter
+  Frag<T> wf[2][NJ];  // weight fragments of the stage's first and second half of K
   auto read_a = [&](int buf, int ks, int h, int i) {
-    xa[ks][i] = *reinterpret_cast<const bf16x8*>(smem + oa[buf][ks] + (h * SH + i) * 16 * C::RB);
+    xa[ks][i] = *reinterpret_cast<const Frag<T>*>(smem + oa[buf][ks] + (h * SH + i) * 16 * C::RB);
   };
   auto read_w = [&](int buf, int ks, int u) {
-    wf[ks][u] = *reinterpret_cast<const bf16x8*>(smem + ob[buf][ks] + (u / SN) * C::B_BYTES +
+    wf[ks][u] = *reinterpret_cast<const Frag<T>*>(smem + ob[buf][ks] + (u / SN) * C::B_BYTES +
                                                  (u % SN) * 16 * C::RB);
   };
   // Rows of this wave's tile that exist: with at most half of them the wave
@@ -567,7 +602,7 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs& g
         for (int n = 0; n < QM; ++n) {
           dma(n);
           const int i = n / NJ, j = n % NJ;
-          mma16(acc[j / SN][h * SH + i][j % SN], wf[ks][j], xa[ks][i]);
+          mma_step<SN, NJ>(acc, h * SH + i, j, wf[ks], xa[ks][i]);
           if (n < nr) rd(n);
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -685,7 +720,7 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs& g
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[0][i][j][v] += xv[i][j][v];
   }
-  if constexpr (GATEUP && OUT_CPOL != 0) {
+  if constexpr (GATEUP && OUT_CPOL != 0 && BF16) {
     if (!g.halves) {
       // Device-scope stores of whole lines: the SwiGLU tile goes to LDS
       // first (free after the K loop; 16-byte chunk c of tile row r at slot
@@ -727,7 +762,7 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs& g
       return;
     }
   }
-  if constexpr (GATEUP) {
+  if constexpr (GATEUP && BF16) {
     if (g.halves) {
       // The BM x 2*BN output tile (slice b at columns ntile*2*BN + b*BN + ..)
       // goes to LDS first (the stage buffers are free after the K loop;
@@ -786,19 +821,20 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs& g
     for (int j = 0; j < SN; ++j) {
       const int n = n0 + wn_e * C::WTN + j * 16 + ncol_e;
       if (n >= N) continue;
-      bf16x4 o;
+      typedef T Out4 __attribute__((ext_vector_type(4)));
+      Out4 o;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         float val = acc[0][i][j][v];
-        if constexpr (GATEUP) val = silu_f(val) * acc[C::NB - 1][i][j][v];
+        if constexpr (GATEUP) {
+          const float u = acc[C::NB - 1][i][j][v];
+          if constexpr (BF16) val = silu_f(val) * u;
+          else val = val / (1.0f + expf(-val)) * u;
+        }
         if constexpr (RESID) val *= res.scale;
-        o[v] = (bf16)val;
+        o[v] = (T)val;
       }
-      if constexpr (OUT_CPOL != 0)
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), out_rsrc,
-                                              (uint32_t)(((size_t)m * N + n) * 2), 0, OUT_CPOL);
-      else
-        *reinterpret_cast<bf16x4*>(out + (size_t)m * N + n) = o;
+      *reinterpret_cast<Out4*>(out + (size_t)m * N + n) = o;
     }
   }
 }
@@ -820,18 +856,18 @@ __device__ __forceinline__ void tile_coords(int t, int ntn, int m_tiles, int& mt
   }
 }
 
-template <int BM, int BN, int WM, int WN, bool GATEUP, int NST, int GM, int PERSIST,
+template <typename T, int BM, int BN, int WM, int WN, bool GATEUP, int NST, int GM, int PERSIST,
           bool RESID = false>
 __global__ __launch_bounds__(WM* WN* kWave) __attribute__((amdgpu_waves_per_eu(1, 2)))
-void grouped_gemm_dma(const bf16* __restrict__ A, const int32_t* __restrict__ gather, int kdiv,
+void grouped_gemm_dma(const T* __restrict__ A, const int32_t* __restrict__ gather, int kdiv,
                       int a_rows, const int32_t* __restrict__ offsets, int E, int rows,
-                      const bf16* __restrict__ B0, const bf16* __restrict__ B1, int N, int K,
-                      bf16* __restrict__ out, int n_tiles_n, int n_tiles, GemmResid res) {
-  using C = DmaCfg<BM, BN, WM, WN, GATEUP, NST>;
+                      const T* __restrict__ B0, const T* __restrict__ B1, int N, int K,
+                      T* __restrict__ out, int n_tiles_n, int n_tiles, GemmResid res) {
+  using C = DmaCfg<T, BM, BN, WM, WN, GATEUP, NST>;
   __shared__ __align__(1024) unsigned char smem[NST * C::STAGE];
-  const GemmArgs g{A, gather, kdiv, a_rows, B0, B1, N, K, out, 0u, res, false};
+  const GemmArgs<T> g{A, gather, kdiv, a_rows, B0, B1, N, K, out, 0u, res, false};
   auto run_tile = [&](const int e, const int row0, const int row_end, const int ntile) {
-    gemm_tile<BM, BN, WM, WN, GATEUP, NST, RESID, 0>(smem, g, e, row0, row_end, ntile);
+    gemm_tile<T, BM, BN, WM, WN, GATEUP, NST, RESID, 0>(smem, g, e, row0, row_end, ntile);
   };
 
   // M-tiles that hold rows (persistent form: the tile list is split over
@@ -960,7 +996,7 @@ void ffn_fused_dma(const bf16* __restrict__ A, const int32_t* __restrict__ gathe
   // one tile shape for both GEMMs: BM rows x (BN gate + BN up) columns, or
   // BM rows x 2*BN down columns read as two BN-row slices of W_d (the same
   // operand loads, LDS layout and MFMA sequence; only the epilogue differs)
-  using C = DmaCfg<BM, BN, WM, WN, true, NST>;
+  using C = DmaCfg<bf16, BM, BN, WM, WN, true, NST>;
   __shared__ __align__(1024) unsigned char smem[NST * C::STAGE];
   __shared__ int s_item[2];  // alternate slots: a slot is rewritten one barrier after it is read
   __shared__ int s_tab[3 * kTileTab];
@@ -1066,11 +1102,11 @@ void ffn_fused_dma(const bf16* __restrict__ A, const int32_t* __restrict__ gathe
       }
       // h is stored past the XCD's L2 (other XCDs read it in this launch), y
       // as usual (the next kernel reads it)
-      const GemmArgs g = gu ? GemmArgs{A, gather, kdiv, a_rows, wg, wu, F, d, h,
+      const GemmArgs<bf16> g = gu ? GemmArgs<bf16>{A, gather, kdiv, a_rows, wg, wu, F, d, h,
                                        (uint32_t)rows * F * 2u, GemmResid{}, false}
-                            : GemmArgs{h, nullptr, 1, rows, wd, nullptr, d, F, y,
+                            : GemmArgs<bf16>{h, nullptr, 1, rows, wd, nullptr, d, F, y,
                                        (uint32_t)rows * d * 2u, GemmResid{}, true};
-      gemm_tile<BM, BN, WM, WN, true, NST, false, kScDevice>(
+      gemm_tile<bf16, BM, BN, WM, WN, true, NST, false, kScDevice>(
           smem, g, e, row0, row_end, nt, gu && pending >= 0 ? &ready[pending] : nullptr);
       if (gu) pending = mt;
     }
@@ -1419,7 +1455,9 @@ __global__ __launch_bounds__(256) void ffn_stream_bf16(
 }
 
 
-// ---- fp32 path: plain FMA kernels (small shapes) ---------------------------
+// ---- fp32 with operands past the tiled kernel's 2 GiB offsets: plain FMA ------
+constexpr long long kF32Range = (1ll << 31) - 64;
+
 __device__ int expert_of_row(const int32_t* __restrict__ offsets, int E, int rows, int row) {
   for (int e = 0; e < E; ++e) {
     int a = min(max(offsets[e], 0), rows);
@@ -1480,22 +1518,26 @@ int device_cus() {
 }
 
 template <int BM, int BN, int WM, int WN, int NST, int GM, int PERSIST, bool GATEUP,
-          bool RESID = false>
-void launch_gemm_dma(const bf16* A, const int32_t* gather, int kdiv, int a_rows,
-                     const int32_t* offsets, int E, int rows, const bf16* B0, const bf16* B1,
-                     int N, int K, bf16* out, hipStream_t s, const char* name,
+          bool RESID = false, typename T>
+void launch_gemm_dma(const T* A, const int32_t* gather, int kdiv, int a_rows,
+                     const int32_t* offsets, int E, int rows, const T* B0, const T* B1,
+                     int N, int K, T* out, hipStream_t s, const char* name,
                      GemmResid res = GemmResid{}) {
   const int ntn = ceil_div(N, BN);
   const int max_mt = ceil_div(rows, BM) + E;  // sum_e ceil(M_e/BM) <= rows/BM + E
   const long long n_tiles = (long long)max_mt * ntn;
   long long nb = (n_tiles + 7) / 8 * 8;
   if (PERSIST) {
-    static const int cus = device_cus();
-    nb = nb < cus ? nb : cus;
+    // as many workgroups as the CUs hold at once: by LDS, and two waves a SIMD
+    using C = DmaCfg<T, BM, BN, WM, WN, GATEUP, NST>;
+    constexpr int by_lds = 160 * 1024 / (NST * C::STAGE), by_waves = 8 / C::NW;
+    constexpr int per_cu = by_lds < by_waves ? by_lds : by_waves;
+    static const int slots = device_cus() * (per_cu > 1 ? per_cu : 1);
+    nb = nb < slots ? nb : slots;
   }
   dim3 grid((unsigned)nb);
   ProfileScope ps(name, s);
-  FOE_LAUNCH((grouped_gemm_dma<BM, BN, WM, WN, GATEUP, NST, GM, PERSIST, RESID>),
+  FOE_LAUNCH((grouped_gemm_dma<T, BM, BN, WM, WN, GATEUP, NST, GM, PERSIST, RESID>),
              grid, dim3(WM * WN * kWave), 0, s, A, gather, kdiv, a_rows, offsets, E, rows, B0, B1,
              N, K, out, ntn, (int)n_tiles, res);
 }
@@ -1534,6 +1576,28 @@ hipError_t launch_expert_ffn_ex(foe_dtype dt, int E, int d, int F, int rows, con
   if (rows == 0) return hipSuccess;
   if (dt == FOE_F32) {
     float* h = reinterpret_cast<float*>(scratch);
+    // fp32 products on the matrix cores through the tiled kernel (768 rows, 8
+    // experts, d 768, F 512: gate/up 2540 -> 21 us, down 1200 -> 14; 8192 rows,
+    // 16 experts, d = F = 1024: 316 + 163 us, 108 TFLOP/s; 64-row tiles, two
+    // workgroups per CU: 128-row ones took 31 + 24 and 362 + 200).  A thread
+    // per output read a weight row of its own, 64 rows to a wave instruction.
+    // The loads reach a gathered source, and 64 rows of any operand, through
+    // offsets below 2^31; larger ones take the plain kernels below.
+    const long long widest = d > F ? d : F;
+    if (widest * 256 <= kF32Range &&
+        (gather == nullptr || (long long)a_rows * d * 4 <= kF32Range)) {
+      const float* xa = reinterpret_cast<const float*>(A);
+      DmaLaunch<FOE_F32_GU>::run<true>(xa, gather, kdiv, a_rows, offsets, E, rows,
+                                       reinterpret_cast<const float*>(w_gate),
+                                       reinterpret_cast<const float*>(w_up), F, d, h, s,
+                                       "ffn_gateup_f32");
+      DmaLaunch<FOE_F32_DN>::run<false>(static_cast<const float*>(h), (const int32_t*)nullptr, 1,
+                                        rows, offsets, E, rows,
+                                        reinterpret_cast<const float*>(w_down),
+                                        (const float*)nullptr, d, F,
+                                        reinterpret_cast<float*>(y_perm), s, "ffn_down_f32");
+      return hipGetLastError();
+    }
     {
       ProfileScope ps("ffn_gateup_f32", s);
       FOE_LAUNCH(gateup_f32, dim3(ceil_div((long long)rows * F, 256)), dim3(256), 0, s,

@@ -17,8 +17,11 @@ def _dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
 
 
-def _bf16(a):
-    return _dev(a).to(torch.bfloat16)
+DT = {"bf16": (torch.bfloat16, foe.BF16), "f32": (torch.float32, foe.F32)}
+# largest error over the largest value of an expert.  bf16: h and y are rounded
+# (2^-9 each, relative) and cancel in the sums; fp32: sums of up to 520
+# products, 2^-24 each
+TOL = {"bf16": 2e-2, "f32": 1e-5}
 
 
 def _poison(shape, dtype):
@@ -41,22 +44,22 @@ WIDTHS = [(256, 192), (72, 136), (192, 64), (8, 328), (520, 72)]
 
 @pytest.mark.parametrize("rows", list(ROWS))
 @pytest.mark.parametrize("d,F", WIDTHS)
-def test_expert_ffn_tile_edges(rows, d, F):
+@pytest.mark.parametrize("dt", list(DT))
+def test_expert_ffn_tile_edges(rows, d, F, dt):
     counts = ROWS[rows]
     E, R = len(counts), sum(counts)
-    print("expert_ffn edges", rows, d, F, flush=True)
-    inp = synth.make_ffn_inputs(R, E, d, F, seed=R + d, sigma=0.05)
+    print("expert_ffn edges", rows, d, F, dt, flush=True)
+    dtype, code = DT[dt]
+    inp = synth.make_ffn_inputs(R, E, d, F, seed=R + d, sigma=0.05, dtype=dt)
     off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
-    ws = _poison((foe.workspace_bytes("expert_ffn", foe.BF16, 1, R, d, E, 1, F),), torch.uint8)
-    y = foe.expert_ffn(_bf16(inp["x_perm"]), _dev(off), _bf16(inp["w_gate"]), _bf16(inp["w_up"]),
-                       _bf16(inp["w_down"]), y_perm=_poison((R, d), torch.bfloat16), ws=ws)
+    ws = _poison((foe.workspace_bytes("expert_ffn", code, 1, R, d, E, 1, F),), torch.uint8)
+    x, wg, wu, wd = (_dev(inp[n]).to(dtype) for n in ("x_perm", "w_gate", "w_up", "w_down"))
+    y = foe.expert_ffn(x, _dev(off), wg, wu, wd, y_perm=_poison((R, d), dtype), ws=ws)
     got = y.float().cpu().numpy()
     ref = oracle.expert_ffn(inp["x_perm"], off, inp["w_gate"], inp["w_up"], inp["w_down"])
     assert np.isfinite(got).all()
     for e in range(E):
         a, b = off[e], off[e + 1]
         if b > a:
-            # h and y are rounded to bf16 (2^-9 each, relative): 2e-2 of the
-            # largest value holds both with the sums' cancellation
             err = np.abs(got[a:b] - ref[a:b]).max() / np.abs(ref[a:b]).max()
-            assert err <= 2e-2, (rows, e, err)
+            assert err <= TOL[dt], (rows, e, err)
