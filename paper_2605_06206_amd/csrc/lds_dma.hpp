@@ -37,12 +37,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc_u(const void* base, 
 // LDS destination = lds + imm; imm is a constant once the call is inlined
 // (the library is built with optimisation), so the per-instruction LDS
 // addresses cost no registers.  An LDS-DMA load that reads M0 needs one wait
-// state after the scalar write of M0 (the s_nop).
+// state after the scalar write of M0 (the s_nop).  The scalar add also writes
+// SCC: without the clobber the compiler may carry a comparison across it (it
+// did, a loop's exit test, and the loop ended early).
 __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t lds,
                                       int imm) {
   asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voff),
                "s"(r), "s"(lds), "i"(imm)
-               : "memory");
+               : "memory", "scc", "m0");
 }
 // wait until at most N of this wave's vector memory operations are
 // outstanding and its LDS operations are done, then meet the other waves
