@@ -56,6 +56,14 @@
 #ifndef FOE_DMA_TINY
 #define FOE_DMA_TINY 64, 128, 1, 4, 4, 4
 #endif
+// medium row counts (see ffn_form): 128 rows x (64 gate + 64 up) or 128 columns,
+// 4 waves, two workgroups per CU, K walk rotated
+#ifndef FOE_MID_GU
+#define FOE_MID_GU 128, 64, 2, 2, 2, 4, 3
+#endif
+#ifndef FOE_MID_DN
+#define FOE_MID_DN 128, 128, 2, 2, 2, 4, 3
+#endif
 // fp32 expert FFN: gate/up and down tiles (two workgroups per CU)
 #ifndef FOE_F32_GU
 #define FOE_F32_GU 64, 32, 2, 2, 4, 4, 1
@@ -429,7 +437,7 @@ template <typename T, int BM, int BN, int WM, int WN, bool GATEUP, int NST, bool
           int OUT_CPOL>
 __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs<T>& g, const int e_,
                                           const int row0_, const int row_end_, const int ntile_,
-                                          int32_t* signal = nullptr) {
+                                          int32_t* signal = nullptr, const int rot_ = 0) {
   static_assert(!(RESID && GATEUP), "residual epilogue on the plain form only");
   static_assert(sizeof(T) == 2 || OUT_CPOL == 0, "fp32 stores as usual");
   using C = DmaCfg<T, BM, BN, WM, WN, GATEUP, NST>;
@@ -514,8 +522,15 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs<T>
   // (signed, below 2^31: the range stays in scalar instructions.  A vector
   // instruction that wrote it would need wait states before the loads, which
   // the compiler cannot see)
+  // With `rot` the tile walks its stages from stage rot on and around (only
+  // where K is whole stages): tiles that stream weights from memory then read
+  // different columns at any moment instead of crowding the channels that one
+  // column of the 4 KiB-strided rows lies on.
+  const int nkr = (K + BK - 1) / BK;
+  const int rot = __builtin_amdgcn_readfirstlane(K % BK == 0 ? rot_ % nkr : 0);
   auto stage_rsrc = [&](uint64_t base, uint32_t bytes, int kt) {
-    const int k2 = kt * C::RB;
+    const int kr = kt < nkr ? (kt + rot >= nkr ? kt + rot - nkr : kt + rot) : kt;
+    const int k2 = kr * C::RB;
     return make_rsrc_u(reinterpret_cast<const void*>((uintptr_t)(base + (uint32_t)k2)),
                        (uint32_t)max((int)bytes - k2, 0));
   };
@@ -762,7 +777,7 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs<T>
       return;
     }
   }
-  if constexpr (GATEUP && BF16) {
+  if constexpr (GATEUP && OUT_CPOL != 0 && BF16) {
     if (g.halves) {
       // The BM x 2*BN output tile (slice b at columns ntile*2*BN + b*BN + ..)
       // goes to LDS first (the stage buffers are free after the K loop;
@@ -867,7 +882,11 @@ void grouped_gemm_dma(const T* __restrict__ A, const int32_t* __restrict__ gathe
   __shared__ __align__(1024) unsigned char smem[NST * C::STAGE];
   const GemmArgs<T> g{A, gather, kdiv, a_rows, B0, B1, N, K, out, 0u, res, false};
   auto run_tile = [&](const int e, const int row0, const int row_end, const int ntile) {
-    gemm_tile<T, BM, BN, WM, WN, GATEUP, NST, RESID, 0>(smem, g, e, row0, row_end, ntile);
+    // rotated K walk (PERSIST == 3): neighbouring tiles start 7 stages apart,
+    // a step prime to the usual powers of two
+    gemm_tile<T, BM, BN, WM, WN, GATEUP, NST, RESID, 0>(
+        smem, g, e, row0, row_end, ntile, nullptr,
+        PERSIST == 3 ? 7 * (e * n_tiles_n + ntile) : 0);
   };
 
   // M-tiles that hold rows (persistent form: the tile list is split over
@@ -884,7 +903,7 @@ void grouped_gemm_dma(const T* __restrict__ A, const int32_t* __restrict__ gathe
     vm_barrier<0>();  // the previous tile's LDS reads are done everywhere
     run_tile(e, row0, row_end, nt);
   };
-  if constexpr (PERSIST == 2) {
+  if constexpr (PERSIST >= 2) {
     // one workgroup per CU, each XCD walks a contiguous eighth of the tile
     // order (workgroup b runs on XCD b % 8; the grid is a multiple of 8), so
     // the N-tiles of an M-tile and the M-tiles of a segment meet in that
@@ -1565,6 +1584,33 @@ void pick_tile(int E, int rows, int N, int bm, int bn, F&& f) {
 
 }  // namespace
 
+// The form follows from what bounds it, for E experts (of all clusters) and a
+// mean of rows / E rows each; an expert's rows end half a tile into its last
+// tile on average.  Times of a block call at d 2048, F 1024 in us.
+// - under 32 rows the weights are streamed for 32 rows at a time.  With more,
+//   most experts need a second pass over their weights (16 experts: 24 rows 61
+//   against 62 with the medium tiles, 32 rows 68 against 63, 64 rows 137
+//   against 66).
+// - the medium tiles read every weight once for up to 128 rows, by twice as
+//   many workgroups as the large ones.  They win while the large tiles would be
+//   less than 3/8 full (under 96 rows; 64 experts: 64 rows 198 against 242, 128
+//   rows 286 against 245) or while (nearly) all of them run at once, two to a
+//   CU (16 experts: 64 rows 66 against 91, 128 rows 100 against 98, 192 rows 93
+//   against 110, 256 rows 127 against 119; 8 experts: 384 rows 89 against 97,
+//   512 rows 114 against 110; 24 experts, 194 rows, d 1000, F 680: 90 against
+//   95).
+// - the large tiles as one launch of both GEMMs once they fill the chip: before
+//   that the CUs without a gate/up tile take down tiles and wait for their
+//   rows, and the two launches are faster (16 experts: 256 rows 119 against
+//   138, 384 rows 127 against 121, 512 rows 207 against 171).
+FfnForm ffn_form(int E, int F, long long rows) {
+  if (rows < 32LL * E) return FfnForm::kStream;
+  static const int cus = device_cus();
+  if (rows < 96LL * E || (rows / 128.0 + E / 2.0) * ceil_div(F, 64) <= 2.2 * cus)
+    return FfnForm::kMid;
+  return (rows / 256.0 + E / 2.0) * ceil_div(F, 128) < cus ? FfnForm::kLarge : FfnForm::kFused;
+}
+
 size_t ffn_scratch_bytes(foe_dtype dt, int rows, int F) {
   return align_up((size_t)rows * F * (dt == FOE_BF16 ? 2 : 4), 256);
 }
@@ -1619,7 +1665,8 @@ hipError_t launch_expert_ffn_ex(foe_dtype dt, int E, int d, int F, int rows, con
   const bf16* wd = reinterpret_cast<const bf16*>(w_down);
   bf16* h = reinterpret_cast<bf16*>(scratch);
   bf16* y = reinterpret_cast<bf16*>(y_perm);
-  if (rows < 64 * E) {  // few rows per expert: weight-streaming bound
+  const FfnForm form = ffn_form(E, F, rows);
+  if (form == FfnForm::kStream) {
     {
       const int ng = ceil_div(F, 16);
       ProfileScope ps("ffn_gateup", s);
@@ -1634,6 +1681,12 @@ hipError_t launch_expert_ffn_ex(foe_dtype dt, int E, int d, int F, int rows, con
                  dim3(256), 0, s, static_cast<const bf16*>(h), nullptr, 1, rows, offsets, E,
                  rows, wd, nullptr, d, F, y, ng, 1, 0, FusedCombine{});
     }
+  } else if (form == FfnForm::kMid) {
+    DmaLaunch<FOE_MID_GU>::run<true>(xa, gather, kdiv, a_rows, offsets, E, rows, wg, wu, F, d, h,
+                                     s, "ffn_gateup");
+    DmaLaunch<FOE_MID_DN>::run<false>(static_cast<const bf16*>(h), (const int32_t*)nullptr, 1,
+                                      rows, offsets, E, rows, wd, (const bf16*)nullptr, d, F, y, s,
+                                      "ffn_down");
   } else {
     DmaLaunch<FOE_DMA_GU>::run<true>(xa, gather, kdiv, a_rows, offsets, E, rows, wg, wu, F, d, h,
                                      s, "ffn_gateup");
@@ -1666,7 +1719,7 @@ hipError_t launch_expert_ffn_fused(int E, int d, int F, int rows, const void* A,
 bool ffn_sel_ok(foe_dtype dt, int C, int E, int T, int k) {
   const long long R = (long long)T * k;
   return FOE_FFN_SEL && dt == FOE_BF16 && R > 0 && R <= kSelMax &&
-         (long long)C * R < 64LL * C * E;
+         ffn_form(C * E, 128, C * R) == FfnForm::kStream;
 }
 
 hipError_t launch_expert_ffn_sel(int C, int E, int d, int F, int T, int k, const void* x,

@@ -485,12 +485,13 @@ int foe_cluster_block_ex(foe_dtype dt, int C, int T, int d, int E, int k, int F,
     if (e != hipSuccess) return hip_fail(e, "foe_cluster_block/expert_ffn");
     return FOE_OK;
   }
-  // many rows per expert (bf16): both grouped GEMMs in one persistent launch,
+  // many rows (bf16, see ffn_form): both grouped GEMMs in one persistent launch,
   // whose counters the index pass clears.  Its h rows must be whole 128-byte
   // cache lines (F a multiple of 64), so that no line holds rows of two
   // M-tiles: a down tile then never caches part of a row that another tile is
   // still writing.
-  const bool fused = FOE_FFN_FUSED && dt == FOE_BF16 && CR >= 64LL * C * E && F % 64 == 0;
+  const bool fused = FOE_FFN_FUSED && dt == FOE_BF16 && F % 64 == 0 &&
+                     ffn_form(C * E, F, CR) == FfnForm::kFused;
   int32_t* sync = reinterpret_cast<int32_t*>(base + L.sync);
   const int nsync = fused ? (int)ffn_sync_ints(C * E, (int)CR) : 0;
   // 2. dispatch: expert histogram, prefix sum and stable ranks of all clusters

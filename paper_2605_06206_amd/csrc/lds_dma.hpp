@@ -44,7 +44,7 @@ __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, uint32_t voff, u
                                       int imm) {
   asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voff),
                "s"(r), "s"(lds), "i"(imm)
-               : "memory", "scc", "m0");
+               : "memory", "scc");
 }
 // wait until at most N of this wave's vector memory operations are
 // outstanding and its LDS operations are done, then meet the other waves

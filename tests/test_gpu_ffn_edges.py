@@ -1,12 +1,13 @@
-"""The grouped expert FFN at the edges of its tiles, through the C ABI: row
-counts around the tile rows and their halves, K and N remainders, and odd
-numbers of K stages.  Workspace and output start as NaN, so a row or column
-read from outside its operand shows."""
+"""The grouped expert FFN at the edges of its tiles and of the rule that picks
+them, through the C ABI: row counts around the tile rows and their halves, K
+and N remainders, and odd numbers of K stages.  Workspace and output start as
+NaN, so a row or column read from outside its operand shows."""
 
 import numpy as np
 import pytest
 import torch
 
+import block_check as bc
 from oracle import foe_oracle as oracle
 from paper_2605_06206_amd import foe, synth
 
@@ -19,8 +20,8 @@ def _dev(a):
 
 DT = {"bf16": (torch.bfloat16, foe.BF16), "f32": (torch.float32, foe.F32)}
 # largest error over the largest value of an expert.  bf16: h and y are rounded
-# (2^-9 each, relative) and cancel in the sums; fp32: sums of up to 520
-# products, 2^-24 each
+# (2^-9 each, relative) and cancel in the sums; fp32: sums of up to 8320
+# products, each term within 2^-24 of the running sum
 TOL = {"bf16": 2e-2, "f32": 1e-5}
 
 
@@ -29,17 +30,19 @@ def _poison(shape, dtype):
     return torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda").view(dtype).view(shape)
 
 
-# rows per expert; every list averages at least 64 rows (the tiled kernels)
+# rows per expert; every list averages at least 32 rows (the tiled kernels)
 ROWS = {
     "tile edges": [255, 256, 257, 0, 1],
     "half tile edges": [127, 128, 129, 384, 385],
     "16-row edges": [15, 16, 17, 400, 63],
     "one expert": [1000],
     "many small, one large": [3, 0, 70, 700, 5, 64],
+    "medium tiles": [64, 65, 32, 33, 0, 31],
 }
 # (d, F): K stages of 64 columns, so d = 72 is two stages with a remainder of
-# 8, 192 an odd number of stages, and 8 less than one stage
-WIDTHS = [(256, 192), (72, 136), (192, 64), (8, 328), (520, 72)]
+# 8, 192 an odd number of stages, and 8 less than one stage; the wide F of the
+# last two makes enough tiles for the large ones (from 96 rows per expert on)
+WIDTHS = [(256, 192), (72, 136), (192, 64), (8, 328), (520, 72), (72, 8008), (192, 8320)]
 
 
 @pytest.mark.parametrize("rows", list(ROWS))
@@ -63,3 +66,31 @@ def test_expert_ffn_tile_edges(rows, d, F, dt):
         if b > a:
             err = np.abs(got[a:b] - ref[a:b]).max() / np.abs(ref[a:b]).max()
             assert err <= TOL[dt], (rows, e, err)
+
+
+@pytest.mark.parametrize("T,d,E,k,F", [
+    (31, 64, 2, 2, 64),     # 31 and 32 rows per expert: weight stream, medium tiles
+    (32, 64, 2, 2, 64),
+    (95, 64, 2, 2, 64),     # below 96 rows: medium tiles whatever the width
+    (700, 72, 4, 2, 4416),  # both GEMMs in one launch, d off the tile, odd K stages
+    (513, 192, 2, 1, 8384),
+    (700, 72, 4, 2, 4424),  # as two launches of large tiles (F not a multiple of 64)
+])
+def test_block_ffn_forms(T, d, E, k, F):
+    """The block on both sides of the FFN's form rule; every expert row of the
+    update (the output without the residual) against the oracle."""
+    print("block ffn forms", T, d, E, k, F, flush=True)
+    inp = synth.make_block_inputs(dict(dtype="bf16", C=1, T=T, d=d, E=E, k=k, F=F, sigma=0.05,
+                                       seed=T + d, bias=None))
+    cl = inp["clusters"][0]
+    routes = bc.oracle_routes(inp["x"], inp["clusters"], k)
+    assert not bc.exempt_mask(routes).any()
+    ref, _, _ = bc.oracle_block(inp["x"], inp["clusters"], k, None, "renorm", routes=routes)
+    x, wr, wg, wu, wd = (_dev(a).to(torch.bfloat16) for a in (
+        inp["x"], cl["w_router"], cl["w_gate"], cl["w_up"], cl["w_down"]))
+    ws = _poison((foe.workspace_bytes("cluster_block", foe.BF16, 1, T, d, E, k, F),), torch.uint8)
+    got = foe.cluster_block(x, wr[None], None, wg[None], wu[None], wd[None], k, ws=ws,
+                            out=_poison((T, d), torch.bfloat16)).float().cpu().numpy()
+    assert np.isfinite(got).all()
+    e_out, e_upd = bc.block_errors(got, ref, inp["x"], 1, None, "bf16")
+    assert e_out <= bc.TOL["bf16"] and e_upd <= bc.TOL["bf16"], (e_out, e_upd)
