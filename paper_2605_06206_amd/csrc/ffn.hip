@@ -1152,12 +1152,12 @@ void ffn_fused_dma(const bf16* __restrict__ A, const int32_t* __restrict__ gathe
 // All loads of the loop are LDS DMA issued from inline assembly with explicit
 // vmcnt waits, so NS-2 later stages stay in flight while a stage is used.
 
-template <bool GATEUP, int NS, bool SEL>
+template <bool GATEUP, int NS, bool SEL, bool SLOTS = false>
 __global__ __launch_bounds__(256) void ffn_stream_bf16(
     const bf16* __restrict__ A, const int32_t* __restrict__ gather, int kdiv, int a_rows,
     const int32_t* __restrict__ offsets, int E, int rows, const bf16* __restrict__ W0,
     const bf16* __restrict__ W1, int N, int K, bf16* __restrict__ out, int n_groups,
-    int e_per_c, int r_sel, FusedCombine fc) {
+    int e_per_c, int r_sel, int slots, FusedCombine fc) {
   static_assert(NS >= 2 && NS <= 4, "2 to 4 stages");
   constexpr int WPB = 4;
   constexpr int NPW = GATEUP ? 16 : 32;  // output columns per wave
@@ -1173,22 +1173,50 @@ __global__ __launch_bounds__(256) void ffn_stream_bf16(
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
   const int gpe = (n_groups + WPB - 1) / WPB;                           // workgroups per expert
-  const int e = blockIdx.x / gpe;
-  if (e >= E) return;
   const int n0 = ((blockIdx.x % gpe) * WPB + wave) * NPW;
+  // expert e of all clusters; selection mode: expert le of cluster hc
+  int e = blockIdx.x / gpe, hc = 0, le = 0;
+  [[maybe_unused]] uint64_t pairs = 0;  // (SLOTS) the expert's pairs of the cluster, one bit each
+  if constexpr (SEL) {
+    if constexpr (SLOTS) {
+      // Few pairs (at most 64 per cluster): a workgroup takes the s-th
+      // distinct expert of its cluster, so none is launched for most of the
+      // experts without rows, and none of those loads weights.  Lane j holds
+      // pair j's expert; experts are numbered by their first pair.
+      hc = e / slots;
+      const int s = e - hc * slots;
+      const int id = lane < r_sel ? gather[(size_t)hc * r_sel + lane] : -1;
+      const bool ok = id >= 0 && id < e_per_c;
+      uint64_t same = __ballot(ok);
+      for (int b = 0; (1 << b) < e_per_c; ++b) {
+        const uint64_t bb = __ballot((id >> b) & 1);
+        same &= ((id >> b) & 1) ? bb : ~bb;
+      }
+      const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+      uint64_t first = __ballot(ok && (same & below) == 0);
+      for (int i = 0; i < s; ++i) first &= first - 1;
+      if (first == 0) return;  // the same in every wave
+      const int at = __builtin_ctzll(first);
+      le = __builtin_amdgcn_readlane(id, at);
+      pairs = __ballot(ok && id == le);
+      e = hc * e_per_c + le;
+    } else {
+      hc = e / e_per_c;
+      le = e - hc * e_per_c;
+    }
+  }
+  if (e >= E) return;
   int off_a = 0, off_b = 0;
   if constexpr (!SEL) {
     off_a = offsets[e];  // scalar loads, waited on below
     off_b = offsets[e + 1];
   }
-  // selection mode: expert e is expert le of cluster hc
-  const int hc = SEL ? e / e_per_c : 0;
-  const int le = SEL ? e - hc * e_per_c : 0;
   const uint32_t lds0 = lds_addr(smem);
-  if constexpr (SEL) {
+  if constexpr (SEL && !SLOTS) {
     // the cluster's r_sel expert ids go to LDS first (256 per wave instruction)
     const __amdgpu_buffer_rsrc_t sr =
         make_rsrc_u(gather + (size_t)hc * r_sel, (uint32_t)r_sel * 4u);
+    rsrc_settle(sr);
     for (int c = wave * 256; c < r_sel; c += WPB * 256)
       dma16(sr, (uint32_t)(c + 4 * lane) * 4u, lds0 + NS * SB + c * 4, 0);
   }
@@ -1204,6 +1232,9 @@ __global__ __launch_bounds__(256) void ffn_stream_bf16(
   const __amdgpu_buffer_rsrc_t ar = make_rsrc_u(A, (uint32_t)a_rows * K * 2u);
   // output rows of the folded combine (down, selection mode)
   const __amdgpu_buffer_rsrc_t yr = make_rsrc_u(out, (uint32_t)rows * N * 2u);
+  rsrc_settle(wr0);
+  rsrc_settle(wr1);
+  rsrc_settle(ar);
   const int lr = lane >> 4, lc = lane & 15;
   uint32_t wv[8];  // byte offset of this lane's weight chunk in instruction i (stage 0)
   int wk[8];       // its K column
@@ -1246,15 +1277,21 @@ __global__ __launch_bounds__(256) void ffn_stream_bf16(
     // Pair list of this expert in ascending pair order (the stable order of
     // the dispatch): per 256-pair chunk, each wave ballots its matches and
     // the wave counts give the positions.  The weight DMAs stay in flight.
-    if (nks >= NS - 1) vm_wait<8 * (NS - 1)>();
-    else vm_wait<0>();
-    lds_barrier();
-    const int* sel = reinterpret_cast<const int*>(smem + NS * SB);
     int* lw = reinterpret_cast<int*>(smem + NS * SB + SELB);
     int* wc = lw + kSelMax;
     const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     int n = 0;
-    for (int c0 = 0; c0 < r_sel; c0 += WPB * 64) {
+    if constexpr (SLOTS) {  // every wave writes the same list
+      if ((pairs >> lane) & 1) lw[__popcll(pairs & below)] = lane;
+      n = __popcll(pairs);
+      lds_barrier();
+    } else {
+      if (nks >= NS - 1) vm_wait<8 * (NS - 1)>();
+      else vm_wait<0>();
+      lds_barrier();
+    }
+    const int* sel = reinterpret_cast<const int*>(smem + NS * SB);
+    for (int c0 = 0; !SLOTS && c0 < r_sel; c0 += WPB * 64) {
       const int f = c0 + (int)threadIdx.x;
       const bool ok = f < r_sel && sel[f] == le;
       const uint64_t m = __ballot(ok);
@@ -1672,14 +1709,14 @@ hipError_t launch_expert_ffn_ex(foe_dtype dt, int E, int d, int F, int rows, con
       ProfileScope ps("ffn_gateup", s);
       FOE_LAUNCH((ffn_stream_bf16<true, FOE_STREAM_NS, false>), dim3(E * ceil_div(ng, 4)),
                  dim3(256), 0, s, xa, gather, kdiv, a_rows, offsets, E, rows, wg, wu, F, d, h,
-                 ng, 1, 0, FusedCombine{});
+                 ng, 1, 0, 0, FusedCombine{});
     }
     {
       const int ng = ceil_div(d, 32);
       ProfileScope ps("ffn_down", s);
       FOE_LAUNCH((ffn_stream_bf16<false, FOE_STREAM_NS, false>), dim3(E * ceil_div(ng, 4)),
                  dim3(256), 0, s, static_cast<const bf16*>(h), nullptr, 1, rows, offsets, E,
-                 rows, wd, nullptr, d, F, y, ng, 1, 0, FusedCombine{});
+                 rows, wd, nullptr, d, F, y, ng, 1, 0, 0, FusedCombine{});
     }
   } else if (form == FfnForm::kMid) {
     DmaLaunch<FOE_MID_GU>::run<true>(xa, gather, kdiv, a_rows, offsets, E, rows, wg, wu, F, d, h,
@@ -1734,21 +1771,35 @@ hipError_t launch_expert_ffn_sel(int C, int E, int d, int F, int T, int k, const
   const bf16* wd = static_cast<const bf16*>(w_down);
   bf16* h = static_cast<bf16*>(scratch);
   bf16* yo = static_cast<bf16*>(y);
-  {
-    const int ng = ceil_div(F, 16);
-    ProfileScope ps("ffn_gateup", s);
-    FOE_LAUNCH((ffn_stream_bf16<true, FOE_STREAM_NS, true>), dim3(C * E * ceil_div(ng, 4)),
-                       dim3(256), 0, s, xa, topk_idx, k, T, nullptr, C * E, rows, wg, wu, F, d, h,
-                       ng, E, R, FusedCombine{});
-  }
-  {
-    const int ng = ceil_div(d, 32);
-    ProfileScope ps("ffn_down", s);
-    FOE_LAUNCH((ffn_stream_bf16<false, FOE_STREAM_NS, true>),
-                       dim3(C * E * ceil_div(ng, 4)), dim3(256), 0, s,
-                       static_cast<const bf16*>(h), topk_idx, 1, rows, nullptr, C * E, rows, wd,
-                       nullptr, d, F, yo, ng, E, R, fc);
-  }
+  // Workgroups by distinct experts of the pairs instead of by expert: reading
+  // the ids before the first weights costs every workgroup about 0.7 us, and
+  // an expert without rows otherwise takes an eighth of the weight traffic of
+  // one with rows (the stages issued before its list is known), so it pays
+  // while more than about a fifth of the experts stay empty (e^(-R/E)).  One
+  // token, 8 clusters of 16 experts, d 2048, F 1024: gate/up 48 -> 25 us, down
+  // 41 -> 21; 4 tokens 89 -> 80 and 60 -> 53; 16 tokens (not taken): 163 + 95.
+  const int slots = R <= kWave && 2 * R < 3 * E ? (R < E ? R : E) : 0;
+  const int per_c = slots > 0 ? slots : E;
+  auto go = [&](auto by_slot) {
+    constexpr bool SLOTS = decltype(by_slot)::value;
+    {
+      const int ng = ceil_div(F, 16);
+      ProfileScope ps("ffn_gateup", s);
+      FOE_LAUNCH((ffn_stream_bf16<true, FOE_STREAM_NS, true, SLOTS>),
+                 dim3(C * per_c * ceil_div(ng, 4)), dim3(256), 0, s, xa, topk_idx, k, T, nullptr,
+                 C * E, rows, wg, wu, F, d, h, ng, E, R, slots, FusedCombine{});
+    }
+    {
+      const int ng = ceil_div(d, 32);
+      ProfileScope ps("ffn_down", s);
+      FOE_LAUNCH((ffn_stream_bf16<false, FOE_STREAM_NS, true, SLOTS>),
+                 dim3(C * per_c * ceil_div(ng, 4)), dim3(256), 0, s, static_cast<const bf16*>(h),
+                 topk_idx, 1, rows, nullptr, C * E, rows, wd, nullptr, d, F, yo, ng, E, R, slots,
+                 fc);
+    }
+  };
+  if (slots > 0) go(std::true_type{});
+  else go(std::false_type{});
   return hipGetLastError();
 }
 

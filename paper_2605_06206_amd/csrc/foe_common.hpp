@@ -110,7 +110,7 @@ struct RoutePlan {
   int tok_per_blk = 16; // tokens per workgroup (count block)
   int nblk = 0;         // workgroups per cluster
 };
-RoutePlan plan_route(foe_dtype dt, int C, int T, int d, int E, bool zero_counters);
+RoutePlan plan_route(foe_dtype dt, int C, int T, int d, int E, int gating, bool zero_counters);
 hipError_t launch_route(foe_dtype dt, int C, int T, int d, int E, int k, int gating,
                         const void* x, const void* w_router, const float* bias,
                         int32_t* topk_idx, float* topk_w, hipStream_t s,

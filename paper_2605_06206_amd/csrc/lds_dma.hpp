@@ -34,6 +34,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc_u(const void* base, 
   return __builtin_amdgcn_make_buffer_rsrc(p, (short)0, __builtin_amdgcn_readfirstlane(nbytes),
                                            0x00020000);
 }
+// A vector instruction that writes a scalar register (readfirstlane) needs five
+// wait states before a vector memory instruction reads it; the compiler does
+// not see the loads below, so a resource built right before them waits here.
+__device__ __forceinline__ void rsrc_settle(__amdgpu_buffer_rsrc_t r) {
+  asm volatile("s_nop 4" ::"s"(r));
+}
 // LDS destination = lds + imm; imm is a constant once the call is inlined
 // (the library is built with optimisation), so the per-instruction LDS
 // addresses cost no registers.  An LDS-DMA load that reads M0 needs one wait

@@ -702,11 +702,20 @@ hipError_t launch_t(const RoutePlan& p, int C, int T_, int d, int E, int k, int 
 
 }  // namespace
 
-RoutePlan plan_route(foe_dtype dt, int C, int T, int d, int E, bool zero_counters) {
+RoutePlan plan_route(foe_dtype dt, int C, int T, int d, int E, int gating, bool zero_counters) {
   RoutePlan p;
   // several clusters: one pass over x scores all C*E experts (the router
-  // matrices are contiguous) and each cluster takes its top-k from its block
-  p.G = (C > 1 && C * E <= 256) ? C : 1;
+  // matrices are contiguous) and each cluster takes its top-k from its block.
+  // A workgroup per cluster instead reads x once per cluster, but works where
+  // few tokens leave most CUs idle while one workgroup reads every router row
+  // (8 clusters x 8 experts, d 2048: 1 token 15.9 -> 6.3 us, 1000 tokens 15.3 ->
+  // 9.8, 2040 tokens 15.8 -> 14.7, 3000 tokens 15.9 -> 21.3), and past 64 score
+  // columns, where the one-pass kernel has four waves and little in flight (8 x
+  // 32: 3 tokens 47 -> 9, 8000 tokens 97 -> 61).  The global softmax needs all
+  // scores of a token together.
+  const bool spread = gating != FOE_GATE_GLOBAL &&
+                      (C * E > 64 || (T < 2048 && (long long)ceil_div(T, kTok) * C <= 1024));
+  p.G = (C > 1 && C * E <= 256 && !spread) ? C : 1;
   const int Et = p.G * E;
   // buffer offsets are 32-bit: x must span less than 2 GiB
   p.stream = FOE_ROUTE_STREAM && dt == FOE_BF16 && !zero_counters &&
@@ -731,7 +740,7 @@ hipError_t launch_route(foe_dtype dt, int C, int T, int d, int E, int k, int gat
                         int32_t* topk_idx, float* topk_w, hipStream_t s, int32_t* zero_cnt,
                         int zero_per_tok, int32_t* counts) {
   if (T == 0 || C == 0) return hipSuccess;
-  const RoutePlan p = plan_route(dt, C, T, d, E, zero_cnt != nullptr);
+  const RoutePlan p = plan_route(dt, C, T, d, E, gating, zero_cnt != nullptr);
   if (dt == FOE_BF16)
     return launch_t<bf16>(p, C, T, d, E, k, gating, x, w_router, bias, topk_idx, topk_w, s,
                           zero_cnt, zero_per_tok, counts);

@@ -94,3 +94,31 @@ def test_block_ffn_forms(T, d, E, k, F):
     assert np.isfinite(got).all()
     e_out, e_upd = bc.block_errors(got, ref, inp["x"], 1, None, "bf16")
     assert e_out <= bc.TOL["bf16"] and e_upd <= bc.TOL["bf16"], (e_out, e_upd)
+
+
+@pytest.mark.parametrize("T,d,E,k,F,C", [
+    (1, 64, 8, 2, 64, 3),     # two pairs per cluster
+    (5, 72, 32, 4, 136, 2),   # 20 pairs, some experts several times
+    (32, 64, 64, 2, 64, 1),   # 64 pairs: the most that one wave lists
+    (33, 64, 64, 2, 64, 1),   # one token more
+    (3, 64, 100, 1, 64, 2),   # three pairs among 100 experts
+    (11, 64, 8, 1, 64, 1),    # 11 and 12 pairs for 8 experts: both sides of the rule
+    (12, 64, 8, 1, 64, 1),
+])
+def test_block_few_pairs(T, d, E, k, F, C):
+    """Few pairs per cluster: workgroups numbered by distinct expert."""
+    print("block few pairs", T, d, E, k, F, C, flush=True)
+    inp = synth.make_block_inputs(dict(dtype="bf16", C=C, T=T, d=d, E=E, k=k, F=F, sigma=0.05,
+                                       seed=7 * T + d, bias=None))
+    routes = bc.oracle_routes(inp["x"], inp["clusters"], k)
+    assert not bc.exempt_mask(routes).any()
+    ref, _, _ = bc.oracle_block(inp["x"], inp["clusters"], k, None, "renorm", routes=routes)
+    w = {n: _dev(np.stack([cl[n] for cl in inp["clusters"]])).to(torch.bfloat16)
+         for n in ("w_router", "w_gate", "w_up", "w_down")}
+    ws = _poison((foe.workspace_bytes("cluster_block", foe.BF16, C, T, d, E, k, F),), torch.uint8)
+    got = foe.cluster_block(_dev(inp["x"]).to(torch.bfloat16), w["w_router"], None, w["w_gate"],
+                            w["w_up"], w["w_down"], k, ws=ws,
+                            out=_poison((T, d), torch.bfloat16)).float().cpu().numpy()
+    assert np.isfinite(got).all()
+    e_out, e_upd = bc.block_errors(got, ref, inp["x"], C, None, "bf16")
+    assert e_out <= bc.TOL["bf16"] and e_upd <= bc.TOL["bf16"], (e_out, e_upd)
