@@ -1232,9 +1232,7 @@ __global__ __launch_bounds__(256) void ffn_stream_bf16(
   const __amdgpu_buffer_rsrc_t ar = make_rsrc_u(A, (uint32_t)a_rows * K * 2u);
   // output rows of the folded combine (down, selection mode)
   const __amdgpu_buffer_rsrc_t yr = make_rsrc_u(out, (uint32_t)rows * N * 2u);
-  rsrc_settle(wr0);
-  rsrc_settle(wr1);
-  rsrc_settle(ar);
+  rsrc_settle(wr0, wr1);
   const int lr = lane >> 4, lc = lane & 15;
   uint32_t wv[8];  // byte offset of this lane's weight chunk in instruction i (stage 0)
   int wk[8];       // its K column
@@ -1271,6 +1269,7 @@ __global__ __launch_bounds__(256) void ffn_stream_bf16(
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
     if (s < nks) issue_w(s, s);
+  rsrc_settle(ar);
   int a = 0, b = 0;
   const int* lst = reinterpret_cast<const int*>(smem + NS * SB + SELB);
   if constexpr (SEL) {

@@ -40,6 +40,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc_u(const void* base, 
 __device__ __forceinline__ void rsrc_settle(__amdgpu_buffer_rsrc_t r) {
   asm volatile("s_nop 4" ::"s"(r));
 }
+__device__ __forceinline__ void rsrc_settle(__amdgpu_buffer_rsrc_t a, __amdgpu_buffer_rsrc_t b) {
+  asm volatile("s_nop 4" ::"s"(a), "s"(b));
+}
 // LDS destination = lds + imm; imm is a constant once the call is inlined
 // (the library is built with optimisation), so the per-instruction LDS
 // addresses cost no registers.  An LDS-DMA load that reads M0 needs one wait
