@@ -13,6 +13,7 @@
 // that sum and scales by 1/H, so the per-group outputs never reach memory.
 // The kernels below describe their layouts.
 #include <mutex>
+#include <type_traits>
 
 #include "foe_common.hpp"
 #include "lds_dma.hpp"
@@ -23,7 +24,7 @@ namespace {
 // head dimensions the kernels are built for: 128 (the 7B model) and 96 (the
 // 1B model); a K tile row is 256 bytes either way (dims past hd read zeros)
 constexpr int kHdMax = 128;
-constexpr int kQB = 64;   // queries per workgroup and head
+constexpr int kQB = 64;   // rows per workgroup of the preparation pass
 constexpr int kKB = 64;   // keys per block of the V^T layout (its zero padding)
 // floor of the running maximum (log2 units): finite, and far below any score
 constexpr float kMFloor = -1.0e30f;
@@ -141,16 +142,19 @@ __global__ __launch_bounds__(256) void prep_kernel(bf16* __restrict__ qkv, bf16*
 }
 
 // ---- attention ----------------------------------------------------------------
-// Task: 64 queries of NH query heads of one group (the heads share the
+// Task: 32*QS queries of NH query heads of one group (the heads share the
 // group's key/value head and so its LDS tiles).  A workgroup of 8 waves has
-// NP parts of 2*NH waves; wave (part, head hh, query half qw) holds 32
+// NP parts of QS*NH waves; wave (part, head hh, query piece qw) holds 32
 // queries.  The parts split the task's key blocks (part p takes blocks p,
 // p + NP, ...) and merge their partial softmax states through LDS at the end,
 // so that every running workgroup keeps two waves on each SIMD however short
-// its task: two heads per task use 2 parts of 64-key blocks, one head (nq
-// odd) 4 parts of 32-key blocks.  Tasks are numbered longest first; with one
-// workgroup per compute unit the dispatcher hands the next task to the first
-// unit that frees up, which balances the causal walks.
+// its task.  64 queries (QS = 2): two heads per task use 2 parts of 64-key
+// blocks, one head (nq odd) 4 parts of 32-key blocks.  128 queries (QS = 4, for
+// long sequences): two heads use one part, one head 2 parts of 64-key blocks,
+// so each K and V^T tile loaded into LDS serves twice the queries.  Tasks are
+// numbered longest first; with one workgroup per compute unit the dispatcher
+// hands the next task to the first unit that frees up, which balances the
+// causal walks.
 // Each part streams its key blocks (KB keys) through its own 2-stage LDS
 // rings filled by LDS-DMA:
 //   K tile   [KB keys][128 dims], 256-byte rows, 16-byte chunk c in slot
@@ -171,12 +175,14 @@ __global__ __launch_bounds__(256) void prep_kernel(bf16* __restrict__ qkv, bf16*
 // log2), so probabilities stay below 2^8 and the accumulators are rescaled
 // only on those (wave-uniform) steps; the final O / l cancels m exactly.
 // Masking (causal, and keys past S) runs only on the blocks that need it.
-template <int NH, int HD, int NP>
-__global__ __launch_bounds__(NP * NH * 128) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd_kernel(
+template <int NH, int HD, int NP, int QS>
+__global__ __launch_bounds__(NP * NH * QS * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd_kernel(
     const bf16* __restrict__ qkv, const bf16* __restrict__ vt, int S, int s_pad, int nq, int H,
     float c_log2, bf16* __restrict__ out) {
-  constexpr int KB = 128 / NP;          // keys per block (64 with 2 parts, 32 with 4)
-  constexpr int HW = 2 * NH;            // waves per part
+  constexpr int KB = NP == 4 ? 32 : 64; // keys per block
+  constexpr int QB = 32 * QS;           // queries per task and head
+  constexpr int HW = QS * NH;           // waves per part
+  constexpr int NTHR = NP * HW * 64;
   constexpr int KT = KB * kHdMax * 2;   // K tile bytes (256-byte rows)
   constexpr int VT = HD * KB * 2;       // V^T tile bytes (rows of 2 KB bytes)
   constexpr int VC = KB / 8;            // 16-byte chunks of a V^T row
@@ -186,10 +192,11 @@ __global__ __launch_bounds__(NP * NH * 128) __attribute__((amdgpu_waves_per_eu(2
   constexpr int NKS = KB / 16;          // P V key steps per block
   constexpr int PART = 2 * KT + 2 * VT; // LDS bytes per part
   constexpr int KI = KT / 1024 / HW;    // DMA instructions per wave and tile
-  constexpr int VI = VT / 1024 / HW;
+  constexpr int VN = VT / 1024;         // V^T instructions per tile; the last wave may have fewer
+  constexpr int VI = (VN + HW - 1) / HW;
   static_assert(HD == 96 || HD == 128, "head dimension");
-  static_assert((NP == 2 || NP == 4) && NP * NH * 2 == 8, "8 waves: 2 parts x 2 heads or 4 x 1");
-  static_assert(KT % (1024 * HW) == 0 && VT % (1024 * HW) == 0, "DMA splits evenly over the waves");
+  static_assert(NP * HW == 8, "8 waves: parts x heads x 32-query pieces");
+  static_assert(KT % (1024 * HW) == 0 && VT % 1024 == 0, "whole DMA instructions");
   static_assert((NP - 1) * HW * 64 * (HD / 2 + 2) * 4 <= NP * PART, "merge buffers fit in the rings");
   __shared__ __align__(1024) unsigned char smem[NP * PART];
 
@@ -200,17 +207,17 @@ __global__ __launch_bounds__(NP * NH * 128) __attribute__((amdgpu_waves_per_eu(2
   const int hw = wave % HW;          // wave within its part
   const int hw_u = __builtin_amdgcn_readfirstlane(hw);
   const int part_u = __builtin_amdgcn_readfirstlane(part);
-  const int nqb = (S + kQB - 1) / kQB;
+  const int nqb = (S + QB - 1) / QB;
   const int hgs = nq / NH;
   const int P = hgs * H;
   const int r = blockIdx.x;
   const int qb = nqb - 1 - r / P;    // longest walks first
   const int rest = r % P;
   const int grp = rest / hgs;
-  const int head = (rest % hgs) * NH + (hw >> 1);
+  const int head = (rest % hgs) * NH + hw / QS;
   const size_t ld = (size_t)(nq + 2) * HD;
   const bf16* gbase = qkv + (size_t)grp * S * ld;
-  const int q0 = qb * kQB + (hw & 1) * 32;  // this wave's first query
+  const int q0 = qb * QB + (hw % QS) * 32;  // this wave's first query
   const int qi = lane & 31, hl = lane >> 5;
   const int q = q0 + qi;
 
@@ -265,7 +272,8 @@ __global__ __launch_bounds__(NP * NH * 128) __attribute__((amdgpu_waves_per_eu(2
     const uint32_t lv = hbase + 2 * KT + (uint32_t)(i & 1) * VT + (uint32_t)hw_u * VI * 1024;
     const uint32_t vstep = (uint32_t)(NP * i + part) * KB * 2u;
 #pragma unroll
-    for (int j = 0; j < VI; ++j) dma16(rv, voff[j] + vstep, lv, j * 1024);
+    for (int j = 0; j < VI; ++j)
+      if (VN % HW == 0 || hw_u * VI + j < VN) dma16(rv, voff[j] + vstep, lv, j * 1024);
   };
   auto pv = [&](f32x16* oacc, const bf16x8* pf, const unsigned char* vs) {
 #pragma unroll
@@ -298,12 +306,12 @@ __global__ __launch_bounds__(NP * NH * 128) __attribute__((amdgpu_waves_per_eu(2
   // P V steps with P = 0 (the first iteration, and the last one of a part
   // left without a block) may read a V stage no DMA has filled: zero both
   // stages of every part so that they add exact zeros
-  for (int i = tid; i < NP * 2 * (VT / 16); i += NP * NH * 128) {
+  for (int i = tid; i < NP * 2 * (VT / 16); i += NTHR) {
     const int h = i / (2 * (VT / 16)), c = i % (2 * (VT / 16));
     *reinterpret_cast<u32x4*>(smem + h * PART + 2 * KT + c * 16) = u32x4{0u, 0u, 0u, 0u};
   }
 
-  const int nkb = min((qb + 1) * (kQB / KB), (S + KB - 1) / KB);
+  const int nkb = min((qb + 1) * (QB / KB), (S + KB - 1) / KB);
   const int niter = (nkb + NP - 1) / NP;  // every part runs the same iterations
   if (part < nkb) issue_k(0);
   // One key block of a part, in two stretches of branch-free code (scheduling
@@ -567,6 +575,14 @@ SideStream* side_stream_locked() {
   return &sd;
 }
 
+int device_cus() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 8)
+    return 256;
+  return n;
+}
+
 struct AttnWs {
   size_t qkv, vt, o, xs, total;
 };
@@ -642,24 +658,29 @@ hipError_t launch_group_attention(int H, int S, int d, int nq, int hd, float the
   {
     ProfileScope ps("attn_core", s);
     const float c_log2 = 1.4426950408889634f / sqrtf((float)hd);
-    // two heads per task: two parts of 64-key blocks; one head: four parts
-    // of 32-key blocks (8 waves either way)
-    const dim3 g2(nqb * (nq / 2) * H), g1(nqb * nq * H);
-    if (hd == 96) {
-      if (nq % 2 == 0)
-        FOE_LAUNCH((attn_fwd_kernel<2, 96, 2>), g2, dim3(512), 0, s, qkv, vt, S, s_pad, nq, H,
-                   c_log2, o);
-      else
-        FOE_LAUNCH((attn_fwd_kernel<1, 96, 4>), g1, dim3(512), 0, s, qkv, vt, S, s_pad, nq, H,
-                   c_log2, o);
-    } else {
-      if (nq % 2 == 0)
-        FOE_LAUNCH((attn_fwd_kernel<2, 128, 2>), g2, dim3(512), 0, s, qkv, vt, S, s_pad, nq, H,
-                   c_log2, o);
-      else
-        FOE_LAUNCH((attn_fwd_kernel<1, 128, 4>), g1, dim3(512), 0, s, qkv, vt, S, s_pad, nq, H,
-                   c_log2, o);
-    }
+    const bool two = nq % 2 == 0;
+    const int hgs = two ? nq / 2 : nq;
+    // Tasks of 128 queries once they are enough to balance the causal walks
+    // (the longest is twice the mean), from 1.5 tasks per CU with two heads and
+    // 1.25 with one; us of this kernel, 64 and 128 queries: 8 groups, two
+    // heads, hd 128, 4096 tokens 88 and 117, 5600 167 and 167, 6144 200 and
+    // 186, 32768 4640 and 4150; one head, hd 96, 4096 tokens 48.5 and 56, 5000
+    // 81 and 71, 8192 171 and 130.
+    static const int cus = device_cus();
+    const bool wide = (long long)ceil_div(S, 128) * hgs * H * 4 >= (long long)cus * (two ? 6 : 5);
+    auto go = [&](auto hdv) {
+      constexpr int HD = decltype(hdv)::value;
+      auto run = [&](auto kern, int qb) {
+        FOE_LAUNCH(kern, dim3(ceil_div(S, qb) * hgs * H), dim3(512), 0, s, qkv, vt, S, s_pad, nq,
+                   H, c_log2, o);
+      };
+      if (two && wide) run(attn_fwd_kernel<2, HD, 1, 4>, 128);
+      else if (two) run(attn_fwd_kernel<2, HD, 2, 2>, 64);
+      else if (wide) run(attn_fwd_kernel<1, HD, 2, 4>, 128);
+      else run(attn_fwd_kernel<1, HD, 4, 2>, 64);
+    };
+    if (hd == 96) go(std::integral_constant<int, 96>{});
+    else go(std::integral_constant<int, 128>{});
   }
   if (!joined) return hipErrorUnknown;
   if (rs != s && (e = hipStreamWaitEvent(s, side->join, 0)) != hipSuccess) return e;
