@@ -234,6 +234,7 @@ constexpr int kSmallWaves = 16;
 // up to this many pairs per cluster the one-workgroup pass beats the two
 // launches of hist + rank (about 4 µs plus 1 µs per 1000 pairs against 8 µs)
 constexpr int kSmallMaxR = 4096;
+constexpr int kSmallChunks = kSmallMaxR / (kSmallWaves * kWave);  // 64-pair chunks per wave
 
 __global__ __launch_bounds__(kSmallWaves * 64) void index_small_kernel(
     const int32_t* __restrict__ idx_all, int R, int E, int nbits,
@@ -257,12 +258,23 @@ __global__ __launch_bounds__(kSmallWaves * 64) void index_small_kernel(
   const int start = wave * per;
   const int end = min(start + per, R);
   const uint64_t below = lanes_below();
-  for (int f0 = start; f0 < end; f0 += kWave) {
-    const int f = f0 + lane_id();
-    const int e = f < end ? idx[f] : -1;
+  // the wave's ids (up to kSmallChunks * 64) are loaded at once, and kept with
+  // their match masks for the second pass; loaded 64 at a time in both passes,
+  // their latencies added up (4096 pairs 8.2 -> 5.9 us, 2331 x 2 6.0 -> 4.8)
+  int ev[kSmallChunks];
+  uint64_t mv[kSmallChunks];
+#pragma unroll
+  for (int c = 0; c < kSmallChunks; ++c) {
+    const int f = start + c * kWave + lane_id();
+    ev[c] = f < end ? idx[f] : -1;
+  }
+#pragma unroll
+  for (int c = 0; c < kSmallChunks; ++c) {
+    if (start + c * kWave >= end) break;
+    const int e = ev[c];
     const bool ok = e >= 0 && e < E;
-    const uint64_t m = match_expert(e, ok, nbits);
-    if (ok && __popcll(m & below) == 0) wcnt[wave][e] += __popcll(m);
+    mv[c] = match_expert(e, ok, nbits);
+    if (ok && __popcll(mv[c] & below) == 0) wcnt[wave][e] += __popcll(mv[c]);
   }
   __syncthreads();
   if (threadIdx.x < E) {
@@ -287,12 +299,14 @@ __global__ __launch_bounds__(kSmallWaves * 64) void index_small_kernel(
   if (threadIdx.x == 0 && h == (int)gridDim.x - 1)
     offsets_all[(size_t)(h + 1) * E] = row_base + total[E];
   __syncthreads();
-  for (int f0 = start; f0 < end; f0 += kWave) {
-    const int f = f0 + lane_id();
+#pragma unroll
+  for (int c = 0; c < kSmallChunks; ++c) {
+    if (start + c * kWave >= end) break;
+    const int f = start + c * kWave + lane_id();
     const bool valid = f < end;
-    const int e = valid ? idx[f] : -1;
-    const bool ok = valid && e >= 0 && e < E;
-    const uint64_t m = match_expert(e, ok, nbits);
+    const int e = ev[c];
+    const bool ok = e >= 0 && e < E;  // (lanes past the end hold -1)
+    const uint64_t m = mv[c];
     const int r = __popcll(m & below);
     // every lane reads its base before the group's first lane advances it
     // (a wave's LDS operations complete in order)
