@@ -277,8 +277,8 @@ int foe_cluster_block_noalloc(foe_dtype dt, int C, int T, int d, int E, int k, i
  *   ws, ws_bytes              workspace of foe_group_attention_workspace_bytes()
  * All pointers are device memory owned by the caller, 16-byte aligned (the
  * workspace too); the call enqueues work on `stream` and returns.  One of its
- * kernels (the residual sum) runs on a library-owned stream of the current
- * device, forked from `stream` and joined back to it by events, so all of the
+ * kernels (the residual sum, unless x is small) runs on a library-owned stream of
+ * the current device, forked from `stream` and joined back to it by events, so all of the
  * call's work still follows earlier work on `stream` and precedes later work
  * (also under HIP-graph capture, where the fork and join become edges).  bf16 only
  * and hd = 96 or 128 (else FOE_ERR_UNSUPPORTED); H*S*d and H*S*(nq+2)*hd must stay

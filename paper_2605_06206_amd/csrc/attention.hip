@@ -8,10 +8,12 @@
 // Launches: the q/k/v projection of every group (one grouped GEMM with a
 // segment per group), a preparation pass (rotary embedding of q and k in
 // place, value head transposed), the attention (o as [S][H*nq*hd]) with the
-// residual sum sum_h x[h] beside it on a side stream, and the output
+// residual sum sum_h x[h] beside it on a side stream (a short sum in the
+// preparation launch), and the output
 // projection of all groups as one GEMM over K = H*nq*hd whose epilogue adds
 // that sum and scales by 1/H, so the per-group outputs never reach memory.
 // The kernels below describe their layouts.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -42,6 +44,36 @@ constexpr float kMFloor = -1.0e30f;
 #define FOE_ATT_SGB 1
 #endif
 
+// ---- residual sum -------------------------------------------------------------
+// xs = sum_h x[h] in fp32, h = 0..H-1 in order; 8 elements per thread and
+// stride step (thread t of n), so that the output projection's epilogue reads
+// one fp32 plane instead of H bf16 planes.
+__device__ __forceinline__ void xsum(const bf16* __restrict__ x, int H, long long plane,
+                                     float* __restrict__ xs, long long t, long long n) {
+  const long long nvec = plane / 8;
+  for (long long i = t; i < nvec; i += n) {
+    float acc[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+#pragma unroll 4
+    for (int h = 0; h < H; ++h) {
+      const bf16x8 v = *reinterpret_cast<const bf16x8*>(x + (size_t)h * plane + i * 8);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] += (float)v[e];
+    }
+    *reinterpret_cast<f32x4*>(xs + i * 8) = f32x4{acc[0], acc[1], acc[2], acc[3]};
+    *reinterpret_cast<f32x4*>(xs + i * 8 + 4) = f32x4{acc[4], acc[5], acc[6], acc[7]};
+  }
+}
+
+// On a side stream beside the attention (which reads little from HBM), for
+// sums that take longer than a launch.
+__global__ __launch_bounds__(256) void xsum_kernel(const bf16* __restrict__ x, int H,
+                                                   long long plane, float* __restrict__ xs) {
+  xsum(x, H, plane, xs, (long long)blockIdx.x * blockDim.x + threadIdx.x,
+       (long long)gridDim.x * blockDim.x);
+}
+
 // ---- preparation pass ----------------------------------------------------------
 // One workgroup per (64-row block, group).  (1) Rotary embedding of the q and
 // k heads in place: each angle (s / scale) * theta^(-2i/HD) is formed once,
@@ -65,7 +97,9 @@ constexpr int kPrepThr = 1024;
 template <int HD>
 __global__ __launch_bounds__(kPrepThr) void prep_kernel(bf16* __restrict__ qkv,
                                                         bf16* __restrict__ vt, int S, int s_pad,
-                                                        int nq, double log2_theta, double scale) {
+                                                        int nq, int H, double log2_theta,
+                                                        double scale, const bf16* __restrict__ x,
+                                                        long long plane, float* __restrict__ xs) {
   constexpr int CPR = HD / 8;      // 16-byte chunks of a head row
   constexpr int NPC = kKB * CPR;   // value pieces (64 keys x CPR chunks)
   static_assert(NPC <= kPrepThr && HD * 8 <= kPrepThr && kQB * 16 == kPrepThr, "one each");
@@ -75,7 +109,14 @@ __global__ __launch_bounds__(kPrepThr) void prep_kernel(bf16* __restrict__ qkv,
   // holding one key spread over 8 chunks
   __shared__ __align__(16) bf16 vtile[HD * kKB];
   const int tid = threadIdx.x;
-  const int blk = blockIdx.x, grp = blockIdx.y;
+  const int nblk = (S + kQB - 1) / kQB;
+  if ((int)blockIdx.x >= nblk * H) {  // the workgroups past the blocks: the residual sum
+    const int b = blockIdx.x - nblk * H;
+    xsum(x, H, plane, xs, (long long)b * kPrepThr + tid,
+         (long long)(gridDim.x - nblk * H) * kPrepThr);
+    return;
+  }
+  const int blk = blockIdx.x % nblk, grp = blockIdx.x / nblk;
   const size_t ld = (size_t)(nq + 2) * HD;
   bf16* base = qkv + (size_t)grp * S * ld;
   if (tid < HD / 2) inv_freq[tid] = exp2(-2.0 * tid / HD * log2_theta);
@@ -516,30 +557,6 @@ __global__ __launch_bounds__(NP * NH * QS * 64) __attribute__((amdgpu_waves_per_
   }
 }
 
-// ---- residual sum -------------------------------------------------------------
-// xs = sum_h x[h] in fp32, h = 0..H-1 in order; 8 elements per thread and
-// grid-stride step.  It runs on a side stream beside the attention (which
-// reads little from HBM), so the output projection's epilogue reads one fp32
-// plane instead of H bf16 planes.
-__global__ __launch_bounds__(256) void xsum_kernel(const bf16* __restrict__ x, int H,
-                                                   long long plane, float* __restrict__ xs) {
-  const long long nvec = plane / 8;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < nvec;
-       i += (long long)gridDim.x * blockDim.x) {
-    float acc[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-#pragma unroll 4
-    for (int h = 0; h < H; ++h) {
-      const bf16x8 v = *reinterpret_cast<const bf16x8*>(x + (size_t)h * plane + i * 8);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] += (float)v[e];
-    }
-    *reinterpret_cast<f32x4*>(xs + i * 8) = f32x4{acc[0], acc[1], acc[2], acc[3]};
-    *reinterpret_cast<f32x4*>(xs + i * 8 + 4) = f32x4{acc[4], acc[5], acc[6], acc[7]};
-  }
-}
-
 // The side stream of the current device and the two events that fork it
 // from the caller's stream and join it back (created on first use, default
 // priority, kept until the process ends).  The fork / launch / join sequence
@@ -624,35 +641,45 @@ hipError_t launch_group_attention(int H, int S, int d, int nq, int hd, float the
   bf16* vt = reinterpret_cast<bf16*>(base + L.vt);
   const int nqb = ceil_div(S, kQB);
   const int s_pad = nqb * kKB;
-  {
-    ProfileScope ps("attn_prep", s);
-    if (hd == 96)
-      FOE_LAUNCH(prep_kernel<96>, dim3(nqb, H), dim3(kPrepThr), 0, s, qkv, vt, S, s_pad, nq,
-                 log2((double)theta), (double)scale);
-    else
-      FOE_LAUNCH(prep_kernel<128>, dim3(nqb, H), dim3(kPrepThr), 0, s, qkv, vt, S, s_pad, nq,
-                 log2((double)theta), (double)scale);
-  }
-  // the residual sum on the side stream, beside the attention
   float* xs = reinterpret_cast<float*>(base + L.xs);
   const long long plane = (long long)S * d;
-  std::unique_lock<std::mutex> lock(g_side_mu);
-  SideStream* side = side_stream_locked();
-  hipStream_t rs = s;
-  if (side != nullptr && hipEventRecord(side->fork, s) == hipSuccess &&
-      hipStreamWaitEvent(side->s, side->fork, 0) == hipSuccess)
-    rs = side->s;
+  // A short residual sum runs in extra workgroups of the preparation launch: on
+  // the side stream it costs a launch, and the fork and join through events
+  // take longer than the sum.  us a call beside / inside, by bytes of x: 1000
+  // tokens, 8 groups, d 768 (12 MB) 58 / 40; 3000 tokens (37 MB) 92 / 86; d
+  // 2048, 1000 tokens (33 MB) 76 / 71, 2000 tokens (66 MB) 131 / 134, 4096
+  // tokens (134 MB) 220 / 231.
+  const bool inline_sum = plane * H * 2 <= (48LL << 20);
   {
+    ProfileScope ps("attn_prep", s);
+    const int nx = inline_sum ? (int)std::min(256LL, (plane / 8 + kPrepThr - 1) / kPrepThr) : 0;
+    auto prep = [&](auto kern) {
+      FOE_LAUNCH(kern, dim3(nqb * H + nx), dim3(kPrepThr), 0, s, qkv, vt, S, s_pad, nq, H,
+                 log2((double)theta), (double)scale, static_cast<const bf16*>(x), plane, xs);
+    };
+    if (hd == 96) prep(prep_kernel<96>);
+    else prep(prep_kernel<128>);
+  }
+  // the residual sum on the side stream, beside the attention
+  std::unique_lock<std::mutex> lock(g_side_mu, std::defer_lock);
+  SideStream* side = nullptr;
+  hipStream_t rs = s;
+  bool joined = true;
+  if (!inline_sum) {
+    lock.lock();
+    side = side_stream_locked();
+    if (side != nullptr && hipEventRecord(side->fork, s) == hipSuccess &&
+        hipStreamWaitEvent(side->s, side->fork, 0) == hipSuccess)
+      rs = side->s;
     ProfileScope ps("attn_xsum", rs);
     const long long want = ceil_div(plane / 8, 256LL);
 #ifndef FOE_XSUM_WG
 #define FOE_XSUM_WG 256
 #endif
     FOE_LAUNCH(xsum_kernel, dim3((unsigned)(want < FOE_XSUM_WG ? want : FOE_XSUM_WG)), dim3(256), 0,
-               rs,
-               static_cast<const bf16*>(x), H, plane, xs);
+               rs, static_cast<const bf16*>(x), H, plane, xs);
+    joined = rs == s || (hipEventRecord(side->join, rs) == hipSuccess);
   }
-  const bool joined = rs == s || (hipEventRecord(side->join, rs) == hipSuccess);
   {
     ProfileScope ps("attn_core", s);
     const float c_log2 = 1.4426950408889634f / sqrtf((float)hd);
@@ -682,7 +709,7 @@ hipError_t launch_group_attention(int H, int S, int d, int nq, int hd, float the
   }
   if (!joined) return hipErrorUnknown;
   if (rs != s && (e = hipStreamWaitEvent(s, side->join, 0)) != hipSuccess) return e;
-  lock.unlock();
+  if (lock.owns_lock()) lock.unlock();
   // output projection of all groups at once (o is [S][H*nq*hd], w_o
   // [d][H*nq*hd]) with the residual average in its epilogue:
   // r_full = (o w_o^T + xs) / H

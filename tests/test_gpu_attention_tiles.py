@@ -4,9 +4,10 @@ sampled query rows against the per-row oracle."""
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import attention_oracle as ao
-from paper_2605_06206_amd import synth
+from paper_2605_06206_amd import foe, synth
 from test_gpu_attention import TOL, _run, attn_part_err, rel_err, say
 
 pytestmark = pytest.mark.gpu
@@ -38,3 +39,35 @@ def test_group_attention_tile_forms(H, S, d, nq, hd):
     e_full, e_attn = rel_err(got[rows], ref), attn_part_err(got[rows], ref, x[:, rows].mean(axis=0))
     say(f"rel err r_full {e_full:.2e}, attention part {e_attn:.2e}")
     assert e_full <= TOL and e_attn <= TOL
+
+
+@pytest.mark.parametrize("S", [300, 312])
+def test_group_attention_capture_with_and_without_side_stream(S):
+    """The residual sum of 300 rows (49.2 MB of x) runs in the preparation
+    launch, that of 312 (51.1 MB) on the side stream, forked and joined inside
+    the capture: replays give the eager bits, with the workspace poisoned in
+    between, and the residual alone (zero projections) is the mean over groups."""
+    H, d, nq, hd = 8, 10240, 1, 96
+    say("capture", S)
+    gen = torch.Generator(device="cuda").manual_seed(S)
+    x = torch.randn((H, S, d), generator=gen, device="cuda").to(torch.bfloat16)
+    wq = (torch.randn((H, (nq + 2) * hd, d), generator=gen, device="cuda") * 0.01).to(torch.bfloat16)
+    wo = (torch.randn((d, H * nq * hd), generator=gen, device="cuda") * 0.03).to(torch.bfloat16)
+    n = foe.lib().foe_group_attention_workspace_bytes(H, S, d, nq, hd)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    out = torch.empty((S, d), dtype=torch.bfloat16, device="cuda")
+    mean = foe.group_attention(x, wq, torch.zeros_like(wo), nq, 1e4, 1.0, ws=ws).float()
+    ref = x.double().mean(0)
+    # one rounding to bf16 of sums that are exact to 2^-24
+    assert ((mean - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-6).all()
+    eager = foe.group_attention(x, wq, wo, nq, 1e4, 1.0, ws=ws).clone()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        foe.group_attention(x, wq, wo, nq, 1e4, 1.0, out=out, ws=ws)
+    for _ in range(3):
+        ws.fill_(255)
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager)
