@@ -339,7 +339,10 @@ template <typename T> using Frag = T __attribute__((ext_vector_type(16 / sizeof(
 // The compiler does not see an MFMA here: acc_fence() separates the
 // accumulators' first write and last read from the MFMAs by more wait states
 // than the instructions need; inside the loop an accumulator returns after at
-// least one other MFMA.
+// least one other MFMA.  Fragments come from LDS reads, which the compiler waits
+// for; a vector instruction that wrote one (a register copy) would need two
+// wait states before the MFMA: no such copy is within reach of one in the
+// compiled kernels (looked for along every path into each MFMA).
 template <int SN, int NJ, typename Acc>
 __device__ __forceinline__ void mma_step(Acc& acc, int i, int n, const bf16x8 (&w)[NJ], bf16x8 x) {
   asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
