@@ -1490,18 +1490,33 @@ __global__ __launch_bounds__(256) void ffn_stream_bf16(
           float acc[8];
 #pragma unroll
           for (int q = 0; q < 8; ++q) acc[q] = 0.f;
-          for (int h = 0; h < fc.C; ++h) {
-            for (int j = 0; j < fc.k; ++j) {
-              const size_t p = (size_t)h * r_sel + (size_t)t * fc.k + j;
-              const float wj = fc.w[p];
-              const bf16x8 yv = __builtin_bit_cast(
-                  bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
-                              yr, (uint32_t)((p * N + col) * 2), 0, kScDevice));
+          const bf16x8 xv = *reinterpret_cast<const bf16x8*>(fc.x + (size_t)t * N + col);
+          // the token's rows in the order (h, j), NB of them in flight (one at
+          // a time, their latencies added up: 1 token with 16 rows of 8 clusters,
+          // 22.5 -> 18.6 us for the kernel)
+          constexpr int NB = 8;
+          for (int q0 = 0; q0 < need; q0 += NB) {
+            bf16x8 yv[NB];
+            float wq[NB];
 #pragma unroll
-              for (int q = 0; q < 8; ++q) acc[q] = fmaf(wj, (float)yv[q], acc[q]);
+            for (int u = 0; u < NB; ++u) {
+              if (q0 + u < need) {
+                const int h = (q0 + u) / fc.k, j = q0 + u - h * fc.k;
+                const size_t p = (size_t)h * r_sel + (size_t)t * fc.k + j;
+                wq[u] = fc.w[p];
+                yv[u] = __builtin_bit_cast(
+                    bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                                yr, (uint32_t)((p * N + col) * 2), 0, kScDevice));
+              }
+            }
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+              if (q0 + u < need) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) acc[q] = fmaf(wq[u], (float)yv[u][q], acc[q]);
+              }
             }
           }
-          const bf16x8 xv = *reinterpret_cast<const bf16x8*>(fc.x + (size_t)t * N + col);
           bf16x8 o;
 #pragma unroll
           for (int q = 0; q < 8; ++q) o[q] = (bf16)(fc.scale * fmaf(cx, (float)xv[q], acc[q]));
