@@ -120,9 +120,13 @@ __device__ int total_mtiles(const int32_t* __restrict__ offsets, int E, int rows
 // decreasing bound gives an empty segment.  Lane l counts the tiles of a
 // contiguous range of experts; a wave prefix sum locates the lane holding
 // `mt`, which walks its range again to find the expert.
-__device__ bool find_tile(const int32_t* __restrict__ offsets, int E, int rows, int BM, int mt,
+__device__ bool find_tile(const int32_t* __restrict__ offsets_, int E, int rows, int BM, int mt,
                           int& e_out, int& row0, int& row_end) {
-  const int lane = lane_id();
+  // opaque: in a persistent loop what follows from these is formed anew for
+  // every tile (kept across the tile's K loop, which has no register left, it
+  // is spilled)
+  const int32_t* __restrict__ offsets = opaque_uniform(offsets_);
+  const int lane = opaque_int((int)threadIdx.x) & (kWave - 1);
   const int per = (E + kWave - 1) / kWave;
   const int e_begin = min(lane * per, E), e_end = min(e_begin + per, E);
   auto seg = [&](int e, int& a, int& b) {
@@ -139,7 +143,8 @@ __device__ bool find_tile(const int32_t* __restrict__ offsets, int E, int rows, 
   int incl = mine;
 #pragma unroll
   for (int off = 1; off < kWave; off <<= 1) {
-    const int t = __shfl_up(incl, off);
+    // (__shfl_up forms its lane addresses from the hardware's lane number)
+    const int t = __builtin_amdgcn_ds_bpermute((lane - off) * 4, incl);
     if (lane >= off) incl += t;
   }
   const int excl = incl - mine;
@@ -454,8 +459,10 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs<T>
   const int row_end = __builtin_amdgcn_readfirstlane(row_end_);
   const int ntile = __builtin_amdgcn_readfirstlane(ntile_);
   const T* __restrict__ A = g.A;
-  const int32_t* __restrict__ gather = g.gather;
-  const int kdiv = g.kdiv, a_rows = g.a_rows, N = g.N, K = g.K;
+  // opaque, as the thread index below: conditions and divisors made of them
+  // would otherwise be kept from tile to tile in vector registers
+  const int32_t* __restrict__ gather = opaque_uniform(g.gather);
+  const int kdiv = opaque_uniform(g.kdiv), a_rows = g.a_rows, N = g.N, K = opaque_uniform(g.K);
   const T* __restrict__ B0 = g.B0;
   const T* __restrict__ B1 = g.B1;
   T* __restrict__ out = g.out;
@@ -510,7 +517,8 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs<T>
       if (gather == nullptr) {
         off_a[h][q] = ((uint32_t)r * K + kcol(ii)) * ES;
       } else {
-        const int s = (row0 + r < row_end) ? src_row(gather, kdiv, row0 + r, a_rows) : -1;
+        const int rr = opaque_int(row0 + r);
+        const int s = rr < row_end ? src_row(gather, kdiv, rr, a_rows) : -1;
         off_a[h][q] = s < 0 ? kOob : ((uint32_t)s * K + kcol(ii)) * ES;
       }
     }
@@ -1021,15 +1029,18 @@ void ffn_fused_dma(const bf16* __restrict__ A, const int32_t* __restrict__ gathe
   using C = DmaCfg<bf16, BM, BN, WM, WN, true, NST>;
   __shared__ __align__(1024) unsigned char smem[NST * C::STAGE];
   __shared__ int s_item[2];  // alternate slots: a slot is rewritten one barrier after it is read
+  // thread 0's own: its current list, and the index it took for the next item
+  // (in LDS because a tile's K loop leaves no vector register for them)
+  __shared__ int s_list, s_next;
   __shared__ int s_tab[3 * kTileTab];
 
   // the M-tile order: the table (scratch in the stage buffers, which no DMA
   // uses yet), or experts in id order through find_tile past its capacity
   static_assert(NST * C::STAGE >= (4 * kTabMaxE + 1) * 4, "table scratch fits");
-  const int mt_tab = build_tile_table<C::NTHR>(offsets, E, rows, BM,
-                                               reinterpret_cast<int*>(smem), s_tab);
-  const bool tab_ok = mt_tab >= 0 && mt_tab <= kTileTab;
-  const int m_tiles = tab_ok ? mt_tab
+  const int mt_tab = __builtin_amdgcn_readfirstlane(build_tile_table<C::NTHR>(
+      offsets, E, rows, BM, reinterpret_cast<int*>(smem), s_tab));
+  auto tab_ok = [](int n) { return n >= 0 && n <= kTileTab; };
+  const int m_tiles = tab_ok(mt_tab) ? mt_tab
                              : __builtin_amdgcn_readfirstlane(total_mtiles(offsets, E, rows, BM));
   const int ntg = (F + BN - 1) / BN, ntd = (d + 2 * BN - 1) / (2 * BN);
   const int n_gu = m_tiles * ntg, n_all = n_gu + m_tiles * ntd;
@@ -1051,30 +1062,35 @@ void ffn_fused_dma(const bf16* __restrict__ A, const int32_t* __restrict__ gathe
   // belong to workgroups of the grid, which run to their end.
   const bool xq = fl.n_groups >= FOE_FUSED_XCD_MIN_GROUPS;
   const int nper = xq ? (int)gridDim.x / 8 : (int)gridDim.x;
-  int list = xq ? (int)blockIdx.x % 8 : 0;  // thread 0's current list
+  if (threadIdx.x == 0) s_list = xq ? (int)blockIdx.x % 8 : 0;
   auto list_size = [&](int l) { return xq ? fl.size(l) : n_all; };
   auto list_item = [&](int l, int i) { return xq ? fl.item(l, i) : i; };
   // thread 0: the next item after index i of the current list (i from the
   // list's counter), or one taken from the other lists, or -1
   auto next_item = [&](int i) {
+    const int list = s_list;
     if (i < list_size(list)) return list_item(list, i);
     for (int k = 1; xq && k < 8; ++k) {
       const int l = (list + k) % 8;
       const int j = nper + atomicAdd(&sync[l * kLineInts], 1);
       if (j < list_size(l)) {
-        list = l;
+        s_list = l;
         return list_item(l, j);
       }
     }
     return -1;
   };
   if (threadIdx.x == 0) {
-    const int i0 = xq ? (int)blockIdx.x / 8 : (int)blockIdx.x;
+    const int i0 = xq ? (int)blockIdx.x / 8 : (int)blockIdx.x, list = s_list;
     s_item[0] = i0 < list_size(list) ? list_item(list, i0)
                                      : next_item(nper + atomicAdd(&sync[list * kLineInts], 1));
   }
   lds_barrier();
-  int t = s_item[0];
+  // The item and its tile are the same for the whole workgroup: in scalar
+  // registers, since a tile leaves no vector register for what is kept across
+  // it (with 24 values spilled, 8192 rows x 2 in 16 experts wrote 128 MB
+  // instead of the 101 of h and y and took 199 us instead of 191).
+  int t = __builtin_amdgcn_readfirstlane(s_item[0]);
   int slot = 0;
   // M-tile of this workgroup's last gate/up tile, not yet counted in ready[]:
   // it is counted at the next gate/up tile's prologue (whose wait drains the
@@ -1089,8 +1105,7 @@ void ffn_fused_dma(const bf16* __restrict__ A, const int32_t* __restrict__ gathe
     }
   };
   while (t >= 0 && t < n_all) {
-    int next_i = 0;
-    if (threadIdx.x == 0) next_i = nper + atomicAdd(&sync[list * kLineInts], 1);
+    if (threadIdx.x == 0) s_next = nper + atomicAdd(&sync[s_list * kLineInts], 1);
     const bool gu = t < n_gu;
     int mt, nt, e, row0, row_end;
     if (gu)
@@ -1098,10 +1113,10 @@ void ffn_fused_dma(const bf16* __restrict__ A, const int32_t* __restrict__ gathe
     else
       tile_coords<GM>(t - n_gu, ntd, m_tiles, mt, nt);
     bool have;
-    if (tab_ok) {
-      e = s_tab[3 * mt];
-      row0 = s_tab[3 * mt + 1];
-      row_end = s_tab[3 * mt + 2];
+    if (tab_ok(opaque_uniform(mt_tab))) {
+      e = __builtin_amdgcn_readfirstlane(s_tab[3 * mt]);
+      row0 = __builtin_amdgcn_readfirstlane(s_tab[3 * mt + 1]);
+      row_end = __builtin_amdgcn_readfirstlane(s_tab[3 * mt + 2]);
       have = true;
     } else {
       have = find_tile(offsets, E, rows, BM, mt, e, row0, row_end);
@@ -1134,9 +1149,9 @@ void ffn_fused_dma(const bf16* __restrict__ A, const int32_t* __restrict__ gathe
     }
     // the next item in LDS; this item's LDS use is done everywhere
     slot ^= 1;
-    if (threadIdx.x == 0) s_item[slot] = next_item(next_i);
+    if (threadIdx.x == 0) s_item[slot] = next_item(s_next);
     lds_barrier();
-    t = s_item[slot];
+    t = __builtin_amdgcn_readfirstlane(s_item[slot]);
   }
   flush();
 }

@@ -61,6 +61,12 @@ __device__ __forceinline__ int opaque_int(int v) {
   asm volatile("" : "+v"(v));
   return v;
 }
+// the same for a wave-uniform value, kept in scalar registers
+template <typename T>
+__device__ __forceinline__ T opaque_uniform(T v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
 
 // Rotate a 32-bit value right by `sh` lanes inside each row of 16 lanes (DPP).
 template <int SH>
