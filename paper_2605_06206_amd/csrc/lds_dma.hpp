@@ -37,6 +37,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc_u(const void* base, 
 // A vector instruction that writes a scalar register (readfirstlane) needs five
 // wait states before a vector memory instruction reads it; the compiler does
 // not see the loads below, so a resource built right before them waits here.
+// (Other kernels form theirs in scalar instructions or well ahead;
+// tests/test_device_code_cpu.py checks every load of the compiled kernels.  The
+// wait in each load instead costs up to 1.5% of a call.)
 __device__ __forceinline__ void rsrc_settle(__amdgpu_buffer_rsrc_t r) {
   asm volatile("s_nop 4" ::"s"(r));
 }
@@ -48,7 +51,9 @@ __device__ __forceinline__ void rsrc_settle(__amdgpu_buffer_rsrc_t a, __amdgpu_b
 // addresses cost no registers.  An LDS-DMA load that reads M0 needs one wait
 // state after the scalar write of M0 (the s_nop).  The scalar add also writes
 // SCC: without the clobber the compiler may carry a comparison across it (it
-// did, a loop's exit test, and the loop ended early).
+// did, a loop's exit test, and the loop ended early).  M0 is a reserved register,
+// which a clobber list cannot name; the same test checks that nothing else in
+// the compiled kernels uses it.
 __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t lds,
                                       int imm) {
   asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voff),
