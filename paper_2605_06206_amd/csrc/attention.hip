@@ -352,6 +352,11 @@ __global__ __launch_bounds__(NP * NH * QS * 64) __attribute__((amdgpu_waves_per_
 
   const int nkb = min((qb + 1) * (QB / KB), (S + KB - 1) / KB);
   const int niter = (nkb + NP - 1) / NP;  // every part runs the same iterations
+  // 128-query tasks: blocks with a key that one of this wave's queries sees.
+  // The task's last block may lie past all of them (one block, a part's last
+  // iteration): it is left out and not masked, since 0 * V is NaN where a later
+  // token's V is not finite.
+  const int nkb_w = QS == 4 ? min(nkb, (qb * QB + (hw_u % QS) * 32 + 31) / KB + 1) : nkb;
   if (part < nkb) issue_k(0);
   // One key block of a part, in two stretches of branch-free code (scheduling
   // regions) with the masking between them, on the blocks that reach the
@@ -486,7 +491,7 @@ __global__ __launch_bounds__(NP * NH * QS * 64) __attribute__((amdgpu_waves_per_
 #pragma unroll
         for (int v = 0; v < 16; ++v) oacc[t][v] *= alpha;
     }
-    if (kb >= nkb) {  // wave-uniform: this part has no block left
+    if (kb >= nkb_w) {  // wave-uniform: no block left for this wave
       pv(oacc, pf, vs);
       resc = false;
       alpha = 1.f;
@@ -498,7 +503,8 @@ __global__ __launch_bounds__(NP * NH * QS * 64) __attribute__((amdgpu_waves_per_
     const bool edge = kbase + KB - 1 > q0 || kbase + KB > S;  // wave-uniform
     block_step(edge, ks, vs, kbase);
   }
-  // the last block's P V (P = 0 if the part's last iteration had no block)
+  // the last block's P V (P = 0 if the part's last iteration had no block,
+  // whose V stage then holds zeros or an earlier block's V)
   vm_barrier<0>();
   if (resc) {
 #pragma unroll
@@ -506,7 +512,7 @@ __global__ __launch_bounds__(NP * NH * QS * 64) __attribute__((amdgpu_waves_per_
 #pragma unroll
       for (int v = 0; v < 16; ++v) oacc[t][v] *= alpha;
   }
-  pv(oacc, pf, hs + 2 * KT + ((niter + 1) & 1) * VT);
+  if (QS != 4 || (niter - 1) * NP + part_u < nkb_w) pv(oacc, pf, hs + 2 * KT + ((niter + 1) & 1) * VT);
 
   // merge: parts 1 .. NP-1 hand (m, l, O) to their partner wave of part 0
   // through LDS (the rings are free after this barrier); part 0 folds them

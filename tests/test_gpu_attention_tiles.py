@@ -71,3 +71,25 @@ def test_group_attention_capture_with_and_without_side_stream(S):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, eager)
+
+
+@pytest.mark.parametrize("H,S,d,nq,hd", [
+    (64, 700, 64, 2, 128), (64, 700, 64, 2, 96),   # 128-query tasks, one and two key parts
+    (64, 700, 64, 1, 128), (64, 700, 64, 1, 96),
+    (2, 700, 64, 2, 128), (2, 700, 64, 1, 96),     # 64-query tasks
+])
+@pytest.mark.parametrize("t", [64, 192, 640])
+def test_tokens_before_a_non_finite_one_keep_their_bits(H, S, d, nq, hd, t):
+    """A token whose x is infinite makes its k and v non-finite; the rows before
+    it (in 64-key blocks before its own) never see them."""
+    say("non-finite token", (H, S, d, nq, hd, t))
+    gen = torch.Generator(device="cuda").manual_seed(t)
+    x = torch.randn((H, S, d), generator=gen, device="cuda").to(torch.bfloat16)
+    wq = (torch.randn((H, (nq + 2) * hd, d), generator=gen, device="cuda") * 0.1).to(torch.bfloat16)
+    wo = (torch.randn((d, H * nq * hd), generator=gen, device="cuda") * 0.03).to(torch.bfloat16)
+    ref = foe.group_attention(x, wq, wo, nq, 1e4, 1.0).clone()
+    assert torch.isfinite(ref.float()).all()
+    x[0, t] = float("inf")
+    got = foe.group_attention(x, wq, wo, nq, 1e4, 1.0)
+    assert torch.equal(got[:t], ref[:t])
+    assert torch.isnan(got[t].float()).all()
