@@ -119,7 +119,8 @@ __global__ __launch_bounds__(kPrepThr) void prep_kernel(bf16* __restrict__ qkv,
   const int blk = blockIdx.x % nblk, grp = blockIdx.x / nblk;
   const size_t ld = (size_t)(nq + 2) * HD;
   bf16* base = qkv + (size_t)grp * S * ld;
-  if (tid < HD / 2) inv_freq[tid] = exp2(-2.0 * tid / HD * log2_theta);
+  // (the first frequency is 1 for an infinite base too, where 0 * log2 is NaN)
+  if (tid < HD / 2) inv_freq[tid] = tid == 0 ? 1.0 : exp2(-2.0 * tid / HD * log2_theta);
 
   // the value rows of the block: piece tid is key tid / CPR, dims
   // 8 (tid % CPR) .. +8 (the load goes out before the rotation work)

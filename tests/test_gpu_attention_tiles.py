@@ -8,7 +8,7 @@ import torch
 
 from oracle import attention_oracle as ao
 from paper_2605_06206_amd import foe, synth
-from test_gpu_attention import TOL, _run, attn_part_err, rel_err, say
+from test_gpu_attention import TOL, _check, _run, attn_part_err, rel_err, say
 
 pytestmark = pytest.mark.gpu
 
@@ -93,3 +93,15 @@ def test_tokens_before_a_non_finite_one_keep_their_bits(H, S, d, nq, hd, t):
     got = foe.group_attention(x, wq, wo, nq, 1e4, 1.0)
     assert torch.equal(got[:t], ref[:t])
     assert torch.isnan(got[t].float()).all()
+
+
+@pytest.mark.parametrize("theta", [3e38, float("inf")])
+def test_largest_rotary_bases(theta):
+    """The rotary base may be any positive float: with an infinite one the first
+    pair of a head rotates by the position and the others stay."""
+    say("rotary base", theta)
+    inp = synth.make_attention_inputs(dict(H=2, S=40, d=64, nq=2, hd=128, theta=theta, scale=1.0,
+                                           sigma=0.05, seed=3))
+    got = _run(inp)
+    assert np.isfinite(got).all()
+    _check(inp, got)
