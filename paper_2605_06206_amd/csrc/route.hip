@@ -16,6 +16,7 @@
 // Weights: the softmax over the k selected scores of the group, or (global
 // gating) the softmax over all G*E scores of the token, not renormalised.
 #include "lds_dma.hpp"
+#include "rules.hpp"
 
 namespace foe {
 namespace {
@@ -706,15 +707,10 @@ RoutePlan plan_route(foe_dtype dt, int C, int T, int d, int E, int gating, bool 
   RoutePlan p;
   // several clusters: one pass over x scores all C*E experts (the router
   // matrices are contiguous) and each cluster takes its top-k from its block.
-  // A workgroup per cluster instead reads x once per cluster, but works where
-  // few tokens leave most CUs idle while one workgroup reads every router row
-  // (8 clusters x 8 experts, d 2048: 1 token 15.9 -> 6.3 us, 1000 tokens 15.3 ->
-  // 9.8, 2040 tokens 15.8 -> 14.7, 3000 tokens 15.9 -> 21.3), and past 64 score
-  // columns, where the one-pass kernel has four waves and little in flight (8 x
-  // 32: 3 tokens 47 -> 9, 8000 tokens 97 -> 61).  The global softmax needs all
-  // scores of a token together.
-  const bool spread = gating != FOE_GATE_GLOBAL &&
-                      (C * E > 64 || (T < 2048 && (long long)ceil_div(T, kTok) * C <= 1024));
+  // The global softmax needs all scores of a token together; the others may take
+  // a workgroup per cluster (route_per_cluster).
+  const bool spread =
+      gating != FOE_GATE_GLOBAL && route_per_cluster(dt == FOE_BF16, C, T, d, E);
   p.G = (C > 1 && C * E <= 256 && !spread) ? C : 1;
   const int Et = p.G * E;
   // buffer offsets are 32-bit: x must span less than 2 GiB

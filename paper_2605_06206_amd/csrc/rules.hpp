@@ -1,0 +1,47 @@
+// Choices between kernels that depend on sizes alone: plain host code, tested
+// without a GPU.
+#pragma once
+
+namespace foe {
+
+// Renormalised routing of C > 1 clusters: one pass over x that scores all C*E
+// experts in a workgroup per 16 tokens, or a workgroup per cluster and 16 tokens.
+// The second reads x once per cluster, but spreads the work where few tokens leave
+// most CUs idle, and past 64 score columns, where the one-pass kernel has four waves
+// and little in flight.  Both times in us, fitted to 1300 measured sizes (2 to
+// 64 clusters, 8 to 256 columns, 1 to 32768 tokens, d 512 to 7168) within about a
+// tenth; the second is taken where it comes out a tenth faster.  One-pass workgroups
+// beyond a first on each CU (4096 tokens) wait for it (bf16, past 64 columns);
+// per-cluster ones run several to a CU and are bound by x, about 1.3 us per CU
+// and 1024 columns of it.  Measured, one pass and per cluster:
+//   8 x 8, d 2048: 1 token 15.9 and 6.3, 2040 tokens 15.8 and 14.7; d 4096: 2040
+//     tokens 24.6 and 26.4; 8 x 4, d 4096: 2040 tokens 16.2 and 23.8
+//   8 x 32, d 2048: 1 token 47 and 9, 8192 tokens 96 and 42; d 4096: 32768 tokens
+//     635 and 369
+//   8 x 16, d 2048: 2048 tokens 28.9 and 17.8; d 4096: 4096 tokens 45 and 59
+//   32 x 4, d 4096: 256 tokens 70 and 14, 4096 tokens 70 and 164
+//   fp32, d 2048: 4 x 32: 4096 tokens 97 and 48, 32768 tokens 299 and 373
+// Up to 64 columns the one-pass kernels of 2048 tokens and more are always taken.
+inline bool route_per_cluster(bool bf16, int C, int T, int d, int E) {
+  const int Et = C * E;
+  if (C < 2 || (Et <= 64 && T >= 2048)) return false;
+  const double D = d / 1024.0, wg = T / 4096.0;  // workgroups per CU
+  const double sel = Et <= 64 ? 1.0 / 3 : Et <= 128 ? 1.0 : 1.6;  // selection, per cluster
+  double one, per;
+  if (bf16) {
+    one = ((T + 4095) / 4096) * (6 + D * (0.9 + 0.054 * Et) + sel * C);
+    per = 3 + D * (1 + 0.04 * E) + 1.3 * D * C * wg;
+  } else {
+    if (Et <= 64) {
+      one = 3 + D * (2 + 0.16 * Et) + sel * C;
+    } else {
+      const double first = D * (6.5 + 0.29 * Et) + sel * C;
+      const double many = wg * (D * (Et <= 128 ? 8.6 + 0.08 * Et : 0.21 * Et) + 0.3 * C);
+      one = first > many ? first : many;
+    }
+    per = 3 + D * (1.5 + 0.04 * E) + D * (2.1 + 0.11 * E) * C * wg;
+  }
+  return per < 0.9 * one;
+}
+
+}  // namespace foe
