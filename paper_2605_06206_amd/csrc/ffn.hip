@@ -601,9 +601,12 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs<T>
                                                  (u % SN) * 16 * C::RB);
   };
   // Rows of this wave's tile that exist: with at most half of them the wave
-  // leaves out its second half's MFMAs and fragment reads (a variant of the
-  // loop; it meets the same barriers).
-  const bool half_only = row_end - row0 - wm * C::WTM <= C::WTM / 2;
+  // leaves out its second half's MFMAs and fragment reads, with none of them
+  // all (variants of the loop, which meet the same barriers).  A tile of 256
+  // rows with at most 128 then leaves the matrix cores to half of its waves
+  // (block calls: 96 rows in each of 40 experts, d = F = 1024: 108 -> 104 us; 24
+  // x 2 experts of 160 rows, d = F = 2048: 391 -> 378).
+  const int wave_rows = row_end - row0 - wm * C::WTM;
 
   // K steps rounded up to a multiple of NST: steps past K read zeros.
   const int nk = ((K + BK - 1) / BK + NST - 1) / NST * NST;
@@ -611,7 +614,7 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs<T>
   constexpr int NWA = WPW + AH;     // DMA instructions of Q2 and Q3
   constexpr int VM = (NST - 1) * NLD;  // loads in flight behind the awaited ones
   auto iteration = [&](auto hv, int kt, int b) {
-    constexpr bool half = decltype(hv)::value;
+    constexpr bool half = decltype(hv)::value >= 1, none = decltype(hv)::value == 2;
     const int bn = (b + 1) % NST;  // buffer of the next stage
     const int dkt = kt + NST;      // the stage loaded into this buffer
     // quarter q: MFMAs of A half q/2, k32 step q%2, each followed by up to one
@@ -619,12 +622,12 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs<T>
     // queue behind the MFMA, up to one DMA instruction (dma(slot))
     auto quarter = [&](auto qv, auto&& dma, int nr, auto&& rd) {
       constexpr int q = decltype(qv)::value, h = q / 2, ks = q % 2;
-      if constexpr (half && h == 1) {
+      if constexpr (none || (half && h == 1)) {
 #pragma unroll
         for (int n = 0; n < QM; ++n) dma(n);
 #pragma unroll
         for (int n = 0; n < SH + NJ; ++n)
-          if (n < nr) rd(n);
+          if (!none && n < nr) rd(n);
       } else {
 #pragma unroll
         for (int n = 0; n < QM; ++n) {
@@ -712,8 +715,9 @@ __device__ __forceinline__ void gemm_tile(unsigned char* smem, const GemmArgs<T>
     // the last DMAs (zeros past K) land before the buffers are reused
     vm_barrier<0>();
   };
-  if (half_only) k_loop(std::true_type{});
-  else k_loop(std::false_type{});
+  if (wave_rows > C::WTM / 2) k_loop(std::integral_constant<int, 0>{});
+  else if (wave_rows > 0) k_loop(std::integral_constant<int, 1>{});
+  else k_loop(std::integral_constant<int, 2>{});
 
   // Thread indices of the epilogue, taken afresh: address arithmetic on
   // the ones above would be hoisted before the K loop and kept live through

@@ -213,6 +213,30 @@ def test_lds_dma_loads_have_their_wait_states(kernels):
     assert n > 100
 
 
+def _loops(code):
+    """Bodies of the innermost loops: from a branch's target to the branch."""
+    found = []
+    for i, c in enumerate(code):
+        found += [(i, p) for p in c.preds if p > i]
+    inner = [(a, b) for a, b in found
+             if not any(a <= x and y <= b and (x, y) != (a, b) for x, y in found)]
+    return [code[a:b + 1] for a, b in inner]
+
+
+def test_waves_without_rows_run_no_mfmas(kernels):
+    """The 256-row kernels have a K loop with loads and barriers alone, for waves
+    none of whose tile rows exist, beside the full one and the half one."""
+    tiled = {k: c for k, c in kernels.items()
+             if "ffn_fused_dma" in k or ("grouped_gemm_dma" in k and "Li256E" in k)}
+    assert len(tiled) >= 3
+    for name, code in tiled.items():
+        loops = [[c.op for c in body] for body in _loops(code)]
+        loops = [ops for ops in loops if "s_barrier" in ops and
+                 any(op.startswith("buffer_load_dwordx4") for op in ops)]
+        mfmas = sorted({sum(op.startswith("v_mfma") for op in ops) for ops in loops})
+        assert len(mfmas) == 3 and mfmas[0] == 0 and mfmas[2] == 2 * mfmas[1], (name, mfmas)
+
+
 LISTING = """
 x:	file format elf64-amdgpu
 
