@@ -1176,6 +1176,14 @@ void ffn_fused_dma(const bf16* __restrict__ A, const int32_t* __restrict__ gathe
 // All loads of the loop are LDS DMA issued from inline assembly with explicit
 // vmcnt waits, so NS-2 later stages stay in flight while a stage is used.
 
+// Expert whose workgroups list a pair (selection mode).  A pair without an expert
+// (id -1: its token's scores are NaN) goes to the first one, so that its token's
+// arrivals become complete and the output row is written; the combine leaves
+// it out.
+__device__ __forceinline__ int listed_expert(int id, int E) {
+  return (unsigned)id < (unsigned)E ? id : 0;
+}
+
 template <bool GATEUP, int NS, bool SEL, bool SLOTS = false>
 __global__ __launch_bounds__(256) void ffn_stream_bf16(
     const bf16* __restrict__ A, const int32_t* __restrict__ gather, int kdiv, int a_rows,
@@ -1209,8 +1217,8 @@ __global__ __launch_bounds__(256) void ffn_stream_bf16(
       // pair j's expert; experts are numbered by their first pair.
       hc = e / slots;
       const int s = e - hc * slots;
-      const int id = lane < r_sel ? gather[(size_t)hc * r_sel + lane] : -1;
-      const bool ok = id >= 0 && id < e_per_c;
+      const bool ok = lane < r_sel;
+      const int id = ok ? listed_expert(gather[(size_t)hc * r_sel + lane], e_per_c) : -1;
       uint64_t same = __ballot(ok);
       for (int b = 0; (1 << b) < e_per_c; ++b) {
         const uint64_t bb = __ballot((id >> b) & 1);
@@ -1316,7 +1324,7 @@ __global__ __launch_bounds__(256) void ffn_stream_bf16(
     const int* sel = reinterpret_cast<const int*>(smem + NS * SB);
     for (int c0 = 0; !SLOTS && c0 < r_sel; c0 += WPB * 64) {
       const int f = c0 + (int)threadIdx.x;
-      const bool ok = f < r_sel && sel[f] == le;
+      const bool ok = f < r_sel && listed_expert(sel[f], e_per_c) == le;
       const uint64_t m = __ballot(ok);
       if (lane == 0) wc[wave] = __popcll(m);
       lds_barrier();
@@ -1519,12 +1527,14 @@ __global__ __launch_bounds__(256) void ffn_stream_bf16(
           for (int q0 = 0; q0 < need; q0 += NB) {
             bf16x8 yv[NB];
             float wq[NB];
+            int id[NB];
 #pragma unroll
             for (int u = 0; u < NB; ++u) {
               if (q0 + u < need) {
                 const int h = (q0 + u) / fc.k, j = q0 + u - h * fc.k;
                 const size_t p = (size_t)h * r_sel + (size_t)t * fc.k + j;
                 wq[u] = fc.w[p];
+                id[u] = gather[p];
                 yv[u] = __builtin_bit_cast(
                     bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
                                 yr, (uint32_t)((p * N + col) * 2), 0, kScDevice));
@@ -1532,7 +1542,7 @@ __global__ __launch_bounds__(256) void ffn_stream_bf16(
             }
 #pragma unroll
             for (int u = 0; u < NB; ++u) {
-              if (q0 + u < need) {
+              if (q0 + u < need && id[u] == listed_expert(id[u], e_per_c)) {
 #pragma unroll
                 for (int q = 0; q < 8; ++q) acc[q] = fmaf(wq[u], (float)yv[u][q], acc[q]);
               }

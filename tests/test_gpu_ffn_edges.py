@@ -122,3 +122,38 @@ def test_block_few_pairs(T, d, E, k, F, C):
     assert np.isfinite(got).all()
     e_out, e_upd = bc.block_errors(got, ref, inp["x"], C, None, "bf16")
     assert e_out <= bc.TOL["bf16"] and e_upd <= bc.TOL["bf16"], (e_out, e_upd)
+
+
+@pytest.mark.parametrize("T,E,k,C", [
+    (1, 8, 2, 2),     # workgroups by distinct expert
+    (7, 8, 2, 1),
+    (20, 8, 1, 4),    # workgroups by expert
+    (100, 8, 2, 2),   # through the index pass or the stream's parts
+    (300, 4, 2, 1),
+    (700, 2, 2, 1),   # tiles
+])
+def test_block_token_without_an_expert(T, E, k, C):
+    """A token with a NaN selects no expert (its scores are NaN): its output row is
+    the residual in every form, and the other rows do not change."""
+    print("block NaN token", T, E, k, C, flush=True)
+    d, F = 72, 64
+    inp = synth.make_block_inputs(dict(dtype="bf16", C=C, T=T, d=d, E=E, k=k, F=F, sigma=0.05,
+                                       seed=T, bias=None))
+    w = {n: _dev(np.stack([cl[n] for cl in inp["clusters"]])).to(torch.bfloat16)
+         for n in ("w_router", "w_gate", "w_up", "w_down")}
+    x = _dev(inp["x"]).to(torch.bfloat16)
+    nan = [t for t in (0, T // 2) if t < T]
+    bad = x.clone()
+    bad[nan, 3] = float("nan")
+
+    def run(x):
+        ws = _poison((foe.workspace_bytes("cluster_block", foe.BF16, C, T, d, E, k, F),), torch.uint8)
+        return foe.cluster_block(x, w["w_router"], None, w["w_gate"], w["w_up"], w["w_down"], k,
+                                 ws=ws, out=torch.full((T, d), 7.0, dtype=torch.bfloat16,
+                                                       device="cuda")).float().cpu()
+
+    got, ref = run(bad), run(x)
+    expect = ref.clone()
+    expect[nan] = bad.float().cpu()[nan]  # C is a power of two: scale * C * x is x
+    same = (got == expect) | (got.isnan() & expect.isnan())
+    assert same.all(), (~same).nonzero()[:5]
