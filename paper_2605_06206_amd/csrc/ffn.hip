@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "lds_dma.hpp"
+#include "rules.hpp"
 
 // LDS-DMA large-M kernel: (BM, BN, WM, WN, LDS stages, M-tile group of the tile
 // order, persistent)
@@ -1344,14 +1345,17 @@ __global__ __launch_bounds__(256) void ffn_stream_bf16(
     a = min(max(off_a, 0), rows);
     b = max(min(max(off_b, 0), rows), a);
   }
-  if (b == a) {  // uniform over the workgroup; the DMAs land before LDS is released
+  // the passes of 32 rows are dealt to the grid's parts (selection mode)
+  const int first = a + (SEL ? (int)blockIdx.y * 32 : 0);
+  const int stride = SEL ? (int)gridDim.y * 32 : 32;
+  if (first >= b) {  // uniform over the workgroup; the DMAs land before LDS is released
     vm_wait<0>();
     return;
   }
 
-  for (int t0 = a; t0 < b; t0 += 32) {
+  for (int t0 = first; t0 < b; t0 += stride) {
     const int tv = min(32, b - t0);
-    if (t0 != a) {
+    if (t0 != first) {
 #pragma unroll
       for (int s = 0; s < NS - 1; ++s)
         if (s < nks) issue_w(s, s);
@@ -1500,7 +1504,11 @@ __global__ __launch_bounds__(256) void ffn_stream_bf16(
       if (threadIdx.x == 0) *ndone = 0;
       __syncthreads();
       const int need = fc.C * fc.k;
-      for (int i = (int)threadIdx.x; i < b; i += WPB * 64) {
+      // (this part's rows: 32 of every `stride` from `first`)
+      const int mine = (b - first + stride - 1) / stride * 32;
+      for (int j = (int)threadIdx.x; j < mine; j += WPB * 64) {
+        const int i = first + j / 32 * stride + j % 32;
+        if (i >= b) continue;
         const int t = lst[i] / fc.k;
         const int old = atomicAdd(&fc.cnt[(size_t)t * gpe + cg], 1);
         if (old == need - 1) done[atomicAdd(ndone, 1)] = t;
@@ -1675,7 +1683,7 @@ void pick_tile(int E, int rows, int N, int bm, int bn, F&& f) {
 // - under 32 rows the weights are streamed for 32 rows at a time.  With more,
 //   most experts need a second pass over their weights (16 experts: 24 rows 61
 //   against 62 with the medium tiles, 32 rows 68 against 63, 64 rows 137
-//   against 66).
+//   against 66; but see stream_spreads for small products).
 // - the medium tiles read every weight once for up to 128 rows, by twice as
 //   many workgroups as the large ones.  They win while the large tiles would be
 //   less than 3/8 full (under 96 rows; 64 experts: 64 rows 198 against 242, 128
@@ -1801,10 +1809,12 @@ hipError_t launch_expert_ffn_fused(int E, int d, int F, int rows, const void* A,
   return hipGetLastError();
 }
 
-bool ffn_sel_ok(foe_dtype dt, int C, int E, int T, int k) {
+bool ffn_sel_ok(foe_dtype dt, int C, int E, int T, int k, int d, int F) {
   const long long R = (long long)T * k;
-  return FOE_FFN_SEL && dt == FOE_BF16 && R > 0 && R <= kSelMax &&
-         ffn_form(C * E, 128, C * R) == FfnForm::kStream;
+  if (!FOE_FFN_SEL || dt != FOE_BF16 || R <= 0 || R > kSelMax) return false;
+  static const int cus = device_cus();
+  return ffn_form(C * E, F, C * R) == FfnForm::kStream ||
+         stream_spreads(C, E, (int)R, d, F, cus);
 }
 
 hipError_t launch_expert_ffn_sel(int C, int E, int d, int F, int T, int k, const void* x,
@@ -1828,20 +1838,25 @@ hipError_t launch_expert_ffn_sel(int C, int E, int d, int F, int T, int k, const
   // 41 -> 21; 4 tokens 89 -> 80 and 60 -> 53; 16 tokens (not taken): 163 + 95.
   const int slots = R <= kWave && 2 * R < 3 * E ? (R < E ? R : E) : 0;
   const int per_c = slots > 0 ? slots : E;
+  static const int cus = device_cus();
+  auto grid = [&](int ng) {
+    const int wgs = C * per_c * ceil_div(ng, 4);
+    return dim3(wgs, stream_parts(R, E, wgs, cus));
+  };
   auto go = [&](auto by_slot) {
     constexpr bool SLOTS = decltype(by_slot)::value;
     {
       const int ng = ceil_div(F, 16);
       ProfileScope ps("ffn_gateup", s);
       FOE_LAUNCH((ffn_stream_bf16<true, FOE_STREAM_NS, true, SLOTS>),
-                 dim3(C * per_c * ceil_div(ng, 4)), dim3(256), 0, s, xa, topk_idx, k, T, nullptr,
+                 grid(ng), dim3(256), 0, s, xa, topk_idx, k, T, nullptr,
                  C * E, rows, wg, wu, F, d, h, ng, E, R, slots, FusedCombine{});
     }
     {
       const int ng = ceil_div(d, 32);
       ProfileScope ps("ffn_down", s);
       FOE_LAUNCH((ffn_stream_bf16<false, FOE_STREAM_NS, true, SLOTS>),
-                 dim3(C * per_c * ceil_div(ng, 4)), dim3(256), 0, s, static_cast<const bf16*>(h),
+                 grid(ng), dim3(256), 0, s, static_cast<const bf16*>(h),
                  topk_idx, 1, rows, nullptr, C * E, rows, wd, nullptr, d, F, yo, ng, E, R, slots,
                  fc);
     }

@@ -458,7 +458,7 @@ int foe_cluster_block_ex(foe_dtype dt, int C, int T, int d, int E, int k, int F,
   // 1. routing of every cluster in one grid (Section 3.1: one score vector,
   //    per-group top-k); with many pairs it also counts the experts of its
   //    token blocks, the histogram of the dispatch
-  const bool sel = ffn_sel_ok(dt, C, E, T, k);
+  const bool sel = ffn_sel_ok(dt, C, E, T, k, d, F);
   const RoutePlan rp = plan_route(dt, C, T, d, E, gating, sel);
   int32_t* rcnt = reinterpret_cast<int32_t*>(base + L.rcnt);
   const bool use_rc = !sel && index_takes_route_counts(T, E, k, rp.nblk);

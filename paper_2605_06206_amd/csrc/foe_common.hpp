@@ -206,7 +206,7 @@ struct FusedCombine {
 // [C][T*k] itself (no dispatch index pass); the intermediate rows and the
 // output rows y [C*T*k][d] are indexed by pair.  ffn_sel_ok() tells whether
 // the shape takes this form.
-bool ffn_sel_ok(foe_dtype dt, int C, int E, int T, int k);
+bool ffn_sel_ok(foe_dtype dt, int C, int E, int T, int k, int d, int F);
 hipError_t launch_expert_ffn_sel(int C, int E, int d, int F, int T, int k, const void* x,
                                  const int32_t* topk_idx, const void* w_gate, const void* w_up,
                                  const void* w_down, void* y, void* scratch, hipStream_t s,

@@ -44,4 +44,31 @@ inline bool route_per_cluster(bool bf16, int C, int T, int d, int E) {
   return per < 0.9 * one;
 }
 
+// The weight stream from the routing decisions themselves (R pairs per cluster): a
+// workgroup takes 64 gate/up or 128 down columns of an expert, 32 rows in a pass.
+// From 32 rows per expert on, the passes are dealt to as many workgroups as the
+// CUs have room for (a workgroup's LDS fills one), up to 8: one after another, the
+// passes of a skewed router's first expert add up.
+inline int stream_parts(int R, int E, long long workgroups, int cus) {
+  if (R < 32 * E) return 1;
+  const long long p = cus / workgroups;
+  return p < 1 ? 1 : p > 8 ? 8 : (int)p;
+}
+
+// From 32 to 64 rows per expert: the stream instead of the medium tiles, which need an
+// index and a combine launch, where both products leave room for two parts, or
+// one for every 8 experts (the more experts, the more passes a skewed router's
+// first one has).  us a block call, medium tiles and stream: 8 experts of 40 rows,
+// d 768, F 256 in 2 clusters 35 and 25; 12 of 48, d 1280, F 512 45 and 32; with a
+// router skewed as (rank + 1)^-1.2, 16 of 48, d 512, F 256 35 and 43.  On average
+// over 212 drawn sizes with room for two parts 0.71 of the medium tiles' time with
+// a uniform router, 0.73 and 0.82 with one skewed as (rank + 1)^-0.5 and ^-1.2;
+// with less room 0.99, 1.23 and 1.96 (162 sizes).
+inline bool stream_spreads(int C, int E, int R, int d, int F, int cus) {
+  if (R < 32 * E || R >= 64 * E) return false;
+  const long long gu = (long long)C * E * ((F + 63) / 64), dn = (long long)C * E * ((d + 127) / 128);
+  const int parts = E > 16 ? (E + 7) / 8 : 2;
+  return parts * (gu > dn ? gu : dn) <= cus;
+}
+
 }  // namespace foe

@@ -157,3 +157,37 @@ def test_block_token_without_an_expert(T, E, k, C):
     expect[nan] = bad.float().cpu()[nan]  # C is a power of two: scale * C * x is x
     same = (got == expect) | (got.isnan() & expect.isnan())
     assert same.all(), (~same).nonzero()[:5]
+
+
+@pytest.mark.parametrize("T,d,E,k,F,C,skew", [
+    (128, 64, 8, 2, 64, 1, 0.0),      # 32 rows per expert: 8 parts
+    (504, 72, 8, 1, 72, 1, 0.0),      # 63 rows, remainders of both widths
+    (512, 72, 8, 1, 72, 1, 0.0),      # 64 rows: medium tiles
+    (255, 264, 4, 1, 200, 3, 0.5),    # several clusters, skewed
+    (2016, 72, 32, 1, 72, 1, 0.3),    # 4 and 8 parts, experts of 0 to over 256 rows
+    (2016, 72, 32, 1, 72, 1, 9.0),    # all rows at one expert: 63 passes
+    (260, 1032, 8, 1, 1000, 1, 0.0),  # 2 and 3 parts
+    (40, 64, 1, 1, 64, 2, 0.0),       # one expert: 40 rows in two passes
+])
+def test_block_stream_parts(T, d, E, k, F, C, skew):
+    """32 to 64 rows per expert: the weight stream with its passes of 32 rows dealt
+    to parts of the grid."""
+    print("block stream parts", T, d, E, k, F, C, skew, flush=True)
+    bias = None if skew == 0 else (-skew * np.log(np.arange(1, E + 1))).astype(np.float32)
+    inp = synth.make_block_inputs(dict(dtype="bf16", C=C, T=T, d=d, E=E, k=k, F=F, sigma=0.05,
+                                       seed=3 * T + d, bias=None))
+    for cl in inp["clusters"]:
+        cl["bias"] = bias
+    routes = bc.oracle_routes(inp["x"], inp["clusters"], k)
+    assert not bc.exempt_mask(routes).any()
+    ref, _, _ = bc.oracle_block(inp["x"], inp["clusters"], k, None, "renorm", routes=routes)
+    w = {n: _dev(np.stack([cl[n] for cl in inp["clusters"]])).to(torch.bfloat16)
+         for n in ("w_router", "w_gate", "w_up", "w_down")}
+    ws = _poison((foe.workspace_bytes("cluster_block", foe.BF16, C, T, d, E, k, F),), torch.uint8)
+    got = foe.cluster_block(_dev(inp["x"]).to(torch.bfloat16), w["w_router"],
+                            None if bias is None else _dev(np.stack([bias] * C)), w["w_gate"],
+                            w["w_up"], w["w_down"], k, ws=ws,
+                            out=_poison((T, d), torch.bfloat16)).float().cpu().numpy()
+    assert np.isfinite(got).all()
+    e_out, e_upd = bc.block_errors(got, ref, inp["x"], C, None, "bf16")
+    assert e_out <= bc.TOL["bf16"] and e_upd <= bc.TOL["bf16"], (e_out, e_upd)

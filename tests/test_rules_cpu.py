@@ -19,7 +19,11 @@ def rules(tmp_path_factory):
     (tmp / "r.cpp").write_text(
         '#include "rules.hpp"\n'
         'extern "C" int per_cluster(int bf16, int C, int T, int d, int E) {\n'
-        '  return foe::route_per_cluster(bf16 != 0, C, T, d, E);\n}\n')
+        '  return foe::route_per_cluster(bf16 != 0, C, T, d, E);\n}\n'
+        'extern "C" int spreads(int C, int E, int R, int d, int F) {\n'
+        '  return foe::stream_spreads(C, E, R, d, F, 256);\n}\n'
+        'extern "C" int parts(int R, int E, int wgs) {\n'
+        '  return foe::stream_parts(R, E, wgs, 256);\n}\n')
     lib = str(tmp / "r.so")
     subprocess.run([gxx, "-std=c++17", "-O1", "-shared", "-fPIC", "-I", build_mod.CSRC,
                     str(tmp / "r.cpp"), "-o", lib], check=True)
@@ -67,3 +71,32 @@ def test_routing_rule_at_its_ends(rules):
             assert not rules.per_cluster(bf16, 8, T, 2048, 8)       # 64 columns, many tokens
         assert rules.per_cluster(bf16, 64, 1, 8, 4)
         assert rules.per_cluster(bf16, 64, 1, 1 << 20, 4)
+
+
+# (C, E, pairs per cluster, d, F, us with medium tiles, us with the stream in
+# parts), uniform router, measured on 256 CUs
+STREAM = [
+    (1, 8, 320, 384, 384, 32.8, 22.9),
+    (2, 8, 384, 1024, 384, 40.6, 27.5),
+    (1, 12, 576, 1280, 512, 44.7, 32.3),
+    (2, 16, 768, 384, 256, 36.3, 26.4),
+    (1, 16, 1008, 1024, 640, 42.7, 48.2),
+    (4, 8, 504, 384, 1024, 44.8, 49.8),
+    (1, 24, 1344, 640, 640, 42.2, 46.0),
+]
+
+
+@pytest.mark.parametrize("C,E,R,d,F,mid,stream", STREAM)
+def test_32_to_64_rows_take_the_faster_form(rules, C, E, R, d, F, mid, stream):
+    assert bool(rules.spreads(C, E, R, d, F)) == (stream < mid)
+
+
+def test_stream_parts_at_their_ends(rules):
+    assert not rules.spreads(1, 8, 255, 64, 64) and rules.spreads(1, 8, 256, 64, 64)
+    assert rules.spreads(1, 8, 511, 64, 64) and not rules.spreads(1, 8, 512, 64, 64)
+    assert rules.spreads(1, 32, 1024, 64, 128) and not rules.spreads(1, 32, 1024, 64, 129)
+    assert rules.parts(255, 8, 8) == 1          # under 32 rows per expert
+    assert rules.parts(256, 8, 8) == 8
+    assert rules.parts(256, 8, 37) == 6
+    assert rules.parts(256, 8, 128) == 2
+    assert rules.parts(256, 8, 4096) == 1
