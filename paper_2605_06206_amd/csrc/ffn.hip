@@ -22,7 +22,6 @@
 #include <type_traits>
 
 #include "lds_dma.hpp"
-#include "rules.hpp"
 
 // LDS-DMA large-M kernel: (BM, BN, WM, WN, LDS stages, M-tile group of the tile
 // order, persistent)
@@ -1677,31 +1676,9 @@ void pick_tile(int E, int rows, int N, int bm, int bn, F&& f) {
 
 }  // namespace
 
-// The form follows from what bounds it, for E experts (of all clusters) and a
-// mean of rows / E rows each; an expert's rows end half a tile into its last
-// tile on average.  Times of a block call at d 2048, F 1024 in us.
-// - under 32 rows the weights are streamed for 32 rows at a time.  With more,
-//   most experts need a second pass over their weights (16 experts: 24 rows 61
-//   against 62 with the medium tiles, 32 rows 68 against 63, 64 rows 137
-//   against 66; but see stream_spreads for small products).
-// - the medium tiles read every weight once for up to 128 rows, by twice as
-//   many workgroups as the large ones.  They win while the large tiles would be
-//   less than 3/8 full (under 96 rows; 64 experts: 64 rows 198 against 242, 128
-//   rows 286 against 245) or while (nearly) all of them run at once, two to a
-//   CU (16 experts: 64 rows 66 against 91, 128 rows 100 against 98, 192 rows 93
-//   against 110, 256 rows 127 against 119; 8 experts: 384 rows 89 against 97,
-//   512 rows 114 against 110; 24 experts, 194 rows, d 1000, F 680: 90 against
-//   95).
-// - the large tiles as one launch of both GEMMs once they fill the chip: before
-//   that the CUs without a gate/up tile take down tiles and wait for their
-//   rows, and the two launches are faster (16 experts: 256 rows 119 against
-//   138, 384 rows 127 against 121, 512 rows 207 against 171).
-FfnForm ffn_form(int E, int F, long long rows) {
-  if (rows < 32LL * E) return FfnForm::kStream;
+FfnForm ffn_form(int E, int d, int F, long long rows) {
   static const int cus = device_cus();
-  if (rows < 96LL * E || (rows / 128.0 + E / 2.0) * ceil_div(F, 64) <= 2.2 * cus)
-    return FfnForm::kMid;
-  return (rows / 256.0 + E / 2.0) * ceil_div(F, 128) < cus ? FfnForm::kLarge : FfnForm::kFused;
+  return ffn_form(E, d, F, rows, cus);
 }
 
 size_t ffn_scratch_bytes(foe_dtype dt, int rows, int F) {
@@ -1758,7 +1735,7 @@ hipError_t launch_expert_ffn_ex(foe_dtype dt, int E, int d, int F, int rows, con
   const bf16* wd = reinterpret_cast<const bf16*>(w_down);
   bf16* h = reinterpret_cast<bf16*>(scratch);
   bf16* y = reinterpret_cast<bf16*>(y_perm);
-  const FfnForm form = ffn_form(E, F, rows);
+  const FfnForm form = ffn_form(E, d, F, rows);
   if (form == FfnForm::kStream) {
     {
       const int ng = ceil_div(F, 16);
@@ -1813,7 +1790,7 @@ bool ffn_sel_ok(foe_dtype dt, int C, int E, int T, int k, int d, int F) {
   const long long R = (long long)T * k;
   if (!FOE_FFN_SEL || dt != FOE_BF16 || R <= 0 || R > kSelMax) return false;
   static const int cus = device_cus();
-  return ffn_form(C * E, F, C * R) == FfnForm::kStream ||
+  return ffn_form(C * E, d, F, C * R, cus) == FfnForm::kStream ||
          stream_spreads(C, E, (int)R, d, F, cus);
 }
 

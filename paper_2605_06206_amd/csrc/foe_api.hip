@@ -491,7 +491,7 @@ int foe_cluster_block_ex(foe_dtype dt, int C, int T, int d, int E, int k, int F,
   // M-tiles: a down tile then never caches part of a row that another tile is
   // still writing.
   const bool fused = FOE_FFN_FUSED && dt == FOE_BF16 && F % 64 == 0 &&
-                     ffn_form(C * E, F, CR) == FfnForm::kFused;
+                     ffn_form(C * E, d, F, CR) == FfnForm::kFused;
   int32_t* sync = reinterpret_cast<int32_t*>(base + L.sync);
   const int nsync = fused ? (int)ffn_sync_ints(C * E, (int)CR) : 0;
   // 2. dispatch: expert histogram, prefix sum and stable ranks of all clusters

@@ -6,6 +6,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "rules.hpp"
 #include "foe.h"
 
 namespace foe {
@@ -145,11 +146,8 @@ hipError_t launch_permute(foe_dtype dt, int T, int d, int E, int k, const int32_
                           int32_t* row_of, void* x_perm, void* scratch, hipStream_t s);
 
 size_t ffn_scratch_bytes(foe_dtype dt, int rows, int F);
-// form of the bf16 expert FFN: weight stream (few rows per expert), medium
-// tiles, large tiles, large tiles with both GEMMs in one launch (the block's,
-// where F is a multiple of 64; elsewhere the same as kLarge)
-enum class FfnForm { kStream, kMid, kLarge, kFused };
-FfnForm ffn_form(int E, int F, long long rows);
+// the rule of rules.hpp on this device
+FfnForm ffn_form(int E, int d, int F, long long rows);
 hipError_t launch_expert_ffn(foe_dtype dt, int E, int d, int F, int rows, const void* x_perm,
                              const int32_t* offsets, const void* w_gate, const void* w_up,
                              const void* w_down, void* y_perm, void* scratch, hipStream_t s);

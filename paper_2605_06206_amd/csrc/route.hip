@@ -16,7 +16,6 @@
 // Weights: the softmax over the k selected scores of the group, or (global
 // gating) the softmax over all G*E scores of the token, not renormalised.
 #include "lds_dma.hpp"
-#include "rules.hpp"
 
 namespace foe {
 namespace {

@@ -44,6 +44,54 @@ inline bool route_per_cluster(bool bf16, int C, int T, int d, int E) {
   return per < 0.9 * one;
 }
 
+// Form of the bf16 expert FFN: weight stream (few rows per expert), medium tiles,
+// large tiles, large tiles with both GEMMs in one launch (the block's, where F is
+// a multiple of 64; elsewhere the same as kLarge).
+enum class FfnForm { kStream, kMid, kLarge, kFused };
+
+// The form for E experts (of all clusters) and a mean of rows / E rows each; an
+// expert's rows end half a tile into its last tile on average.  us of a block call
+// below.
+// - Under 32 rows the weights are streamed for 32 rows at a time.  With more, most
+//   experts need a second pass over their weights (d 2048, F 1024, 16 experts: 24
+//   rows 61 against 62 with the medium tiles, 32 rows 68 against 63, 64 rows 137
+//   against 66; but see stream_spreads).
+// - The medium tiles read every weight once for up to 128 rows, by four times as
+//   many workgroups as the large ones, two to a CU.  They win while the large
+//   tiles would leave CUs idle, or would be less than 3/8 full (under 96 rows),
+//   until the work (tiles x K steps) is long enough that the large tiles'
+//   fewer operand bytes count, or the tiles are too many rounds; unless the
+//   medium ones are more than a round where the large ones run at once.  Medium and
+//   best of the large forms: d = F = 1024, 40 experts: 96 rows 94 and 104; d 768, F
+//   1536, 12 experts: 307 rows 72 and 114; d 2048, F 1024, 24 experts: 128 rows 148
+//   and 119; d 2560, F 1536, 16 experts: 250 rows 194 and 151; 64 experts: d 1280,
+//   F 768, 64 rows 123 and 139, d 4096, F 1024, 95 rows 420 and 384; d 4096, F 512,
+//   32 experts: 160 rows 219 and 193; d 4096, F 256, 48 experts: 450 rows 415 and 295,
+//   but 16 experts: 320 rows 111 and 139.
+// - The large tiles as one launch of both GEMMs once the tiles of one of them fill
+//   the chip: before that the CUs without a gate/up tile take down tiles and wait
+//   for their rows, and two launches are faster (d 2048, F 1024, 16 experts: 256 rows
+//   119 against 138; but d 4096, F 256, 48 experts, 450 rows 342 against 295).
+// The lines are fitted to 520 sizes (4 to 96 experts, 64 to 2000 rows, d 768 to 6144,
+// F 256 to 2048, uniform and skewed routers): 1% above the best form on average.
+inline FfnForm ffn_form(int E, int d, int F, long long rows, int cus) {
+  if (rows < 32LL * E) return FfnForm::kStream;
+  auto tiles = [](double m, int n, int bn) { return m * ((n + bn - 1) / bn); };
+  const double mid = rows / 128.0 + E / 2.0, large = rows / 256.0 + E / 2.0;  // tiles of rows
+  const double work = mid * d * F / cus;
+  const double gu = tiles(mid, F, 64) / cus, dn = tiles(mid, d, 128) / cus;
+  // tiles of experts with a tenth more rows than the mean
+  const double even = (double)E * ((long long)(1.1 * rows / E / 256.0) + 1);
+  const bool idle = tiles(large, F, 128) < cus &&
+                    (tiles(large, d, 256) < cus || tiles(even, d, 256) <= cus);
+  const bool at_once = idle && tiles(even, F, 128) <= cus;
+  if ((rows < 96LL * E && work < 560e3) ||
+      (work < 312e3 && dn <= 4.5 && gu <= (at_once ? 2.2 : 4.0)) ||
+      (work < 352e3 && dn <= 8.3 && gu <= 1.1))
+    return FfnForm::kMid;
+  return idle ? FfnForm::kLarge : FfnForm::kFused;
+}
+
 // The weight stream from the routing decisions themselves (R pairs per cluster): a
 // workgroup takes 64 gate/up or 128 down columns of an expert, 32 rows in a pass.
 // From 32 rows per expert on, the passes are dealt to as many workgroups as the

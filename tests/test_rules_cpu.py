@@ -20,6 +20,8 @@ def rules(tmp_path_factory):
         '#include "rules.hpp"\n'
         'extern "C" int per_cluster(int bf16, int C, int T, int d, int E) {\n'
         '  return foe::route_per_cluster(bf16 != 0, C, T, d, E);\n}\n'
+        'extern "C" int form(int E, int d, int F, long long rows) {\n'
+        '  return (int)foe::ffn_form(E, d, F, rows, 256);\n}\n'
         'extern "C" int spreads(int C, int E, int R, int d, int F) {\n'
         '  return foe::stream_spreads(C, E, R, d, F, 256);\n}\n'
         'extern "C" int parts(int R, int E, int wgs) {\n'
@@ -100,3 +102,48 @@ def test_stream_parts_at_their_ends(rules):
     assert rules.parts(256, 8, 37) == 6
     assert rules.parts(256, 8, 128) == 2
     assert rules.parts(256, 8, 4096) == 1
+
+
+STREAMED, MID, LARGE, FUSED = range(4)
+# (experts, rows, d, F, us with medium tiles, with large ones, with large ones in one
+# launch), measured on 256 CUs; the last two rows with a skewed router
+FORMS = [
+    (24, 1728, 1024, 1024, 57.0, 62.2, 82.9),
+    (40, 2880, 1536, 1024, 122.7, 134.0, 144.0),
+    (64, 6080, 4096, 256, 213.3, 235.2, 226.4),
+    (16, 1776, 2048, 512, 57.8, 75.6, 75.2),
+    (4, 2288, 1024, 384, 44.5, 67.5, 62.4),
+    (12, 5400, 2048, 384, 77.1, 93.4, 99.1),
+    (16, 4096, 2048, 1024, 127.0, 119.0, 138.0),
+    (16, 5120, 4096, 256, 111.0, 145.0, 139.0),
+    (32, 5832, 2048, 704, 131.0, 113.6, 127.6),
+    (32, 2048, 2048, 2048, 200.4, 240.0, 233.7),
+    (24, 3072, 2048, 1024, 148.2, 119.3, 127.0),
+    (12, 3684, 768, 1536, 72.0, 114.0, 102.0),
+    (64, 10240, 5120, 512, 526.2, 376.9, 360.8),
+    (40, 6400, 2048, 1024, 236.5, 233.8, 218.1),
+    (48, 12096, 2560, 640, 267.7, 253.0, 209.3),
+    (8, 15168, 4096, 256, 230.1, 218.5, 198.9),
+    (64, 28800, 2048, 384, 328.9, 302.4, 252.7),
+    (64, 27584, 4096, 1024, 1412.9, 1040.0, 860.5),
+    (48, 21600, 4096, 256, 414.8, 341.9, 294.5),
+    (64, 4096, 2560, 1536, 410.2, 360.3, 346.5),
+]
+
+
+@pytest.mark.parametrize("E,rows,d,F,mid,large,fused", FORMS)
+def test_expert_ffn_takes_the_fastest_form(rules, E, rows, d, F, mid, large, fused):
+    us = {MID: mid, LARGE: large, FUSED: fused}
+    assert rules.form(E, d, F, ctypes.c_longlong(rows)) == min(us, key=us.get)
+
+
+def test_expert_ffn_forms_at_their_ends(rules):
+    def form(E, rows, d, F):
+        return rules.form(E, d, F, ctypes.c_longlong(rows))
+
+    assert form(16, 511, 2048, 1024) == STREAMED and form(16, 512, 2048, 1024) == MID
+    assert form(2, 191, 64, 65536) == MID      # under 96 rows: whatever the tiles
+    assert form(2, 192, 64, 65536) == FUSED
+    assert form(2, 1 << 30, 8, 8) == FUSED     # many tiles, little work
+    assert form(64, 6143, 1 << 14, 1 << 12) == FUSED
+    assert form(1, 1 << 31, 8, 8) == FUSED     # rows past 32 bits
