@@ -92,6 +92,15 @@ inline FfnForm ffn_form(int E, int d, int F, long long rows, int cus) {
   return idle ? FfnForm::kLarge : FfnForm::kFused;
 }
 
+// fp32 expert FFN through the tiled kernel, whose loads reach a gathered source (of
+// gather_rows rows; 0: rows in order), and 64 rows of any operand, through 32-bit
+// offsets below 2^31; larger ones take the plain kernels.
+inline bool f32_tiled(int d, int F, long long gather_rows) {
+  constexpr long long range = (1ll << 31) - 64;
+  const long long widest = d > F ? d : F;
+  return widest * 256 <= range && gather_rows * d * 4 <= range;
+}
+
 // The weight stream from the routing decisions themselves (R pairs per cluster): a
 // workgroup takes 64 gate/up or 128 down columns of an expert, 32 rows in a pass.
 // From 32 rows per expert on, the passes are dealt to as many workgroups as the

@@ -22,6 +22,8 @@ def rules(tmp_path_factory):
         '  return foe::route_per_cluster(bf16 != 0, C, T, d, E);\n}\n'
         'extern "C" int form(int E, int d, int F, long long rows) {\n'
         '  return (int)foe::ffn_form(E, d, F, rows, 256);\n}\n'
+        'extern "C" int f32_tiled(int d, int F, long long gather_rows) {\n'
+        '  return foe::f32_tiled(d, F, gather_rows);\n}\n'
         'extern "C" int spreads(int C, int E, int R, int d, int F) {\n'
         '  return foe::stream_spreads(C, E, R, d, F, 256);\n}\n'
         'extern "C" int parts(int R, int E, int wgs) {\n'
@@ -147,3 +149,17 @@ def test_expert_ffn_forms_at_their_ends(rules):
     assert form(2, 1 << 30, 8, 8) == FUSED     # many tiles, little work
     assert form(64, 6143, 1 << 14, 1 << 12) == FUSED
     assert form(1, 1 << 31, 8, 8) == FUSED     # rows past 32 bits
+
+
+def test_fp32_operands_past_32_bit_offsets_take_the_plain_kernels(rules):
+    def tiled(d, F, rows):
+        return bool(rules.f32_tiled(d, F, ctypes.c_longlong(rows)))
+
+    assert tiled(8, 8, 0) and tiled(1024, 512, 1 << 18)
+    # 64 rows of an operand, every one of them below 2 GiB
+    assert tiled(8388600, 8, 0) and not tiled(8388608, 8, 0)
+    assert tiled(8, 8388600, 0) and not tiled(8, 8388608, 0)
+    # the whole gathered source
+    assert tiled(1024, 512, (1 << 19) - 1) and not tiled(1024, 512, 1 << 19)
+    assert tiled(1024, 512, 0)
+    assert not tiled(8, 8, 1 << 31)
