@@ -54,7 +54,7 @@ if ROOT not in sys.path:
 METRIC = "tokens/s and expert-FFN TFLOP/s per FoE cluster block (decode & prefill), 1 GPU"
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 BF16_MFMA_PEAK_TFLOPS = 2500.0  # dense bf16 MFMA
-FP32_VALU_PEAK_TFLOPS = 157.3   # fp32 vector
+FP32_MFMA_PEAK_TFLOPS = 157.3   # fp32 MFMA
 DEFAULT_CONFIG = "prefill_zipf_bf16"
 # measured after the headline, in the same JSON line
 NESTED_WORKLOADS = ("decode_bf16", "large_bf16", "layer_share_bf16")
@@ -189,7 +189,7 @@ def attention_work(name, cfg):
 def roofline(name, cfg, e_touched, avg_s):
     flops, nbytes = kernel_work(name, cfg, e_touched)
     if cfg["dtype"] == "f32" and name.startswith("ffn"):
-        bound, peak, unit, achieved = "alu", FP32_VALU_PEAK_TFLOPS, "TFLOP/s", flops / avg_s / 1e12
+        bound, peak, unit, achieved = "mfma", FP32_MFMA_PEAK_TFLOPS, "TFLOP/s", flops / avg_s / 1e12
     elif nbytes > 0 and flops / nbytes > BF16_MFMA_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBS * 1e9):
         bound, peak, unit, achieved = "mfma", BF16_MFMA_PEAK_TFLOPS, "TFLOP/s", flops / avg_s / 1e12
     else:
